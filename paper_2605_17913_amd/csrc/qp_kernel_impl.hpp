@@ -452,84 +452,84 @@ QPD void coldot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV
   }
 }
 
-// One 16x16 tile of the rank-16 update on the matrix cores, by a whole wave:
-// M[i][j] -= sum_c L[i][p0+c] sg_c L[j][p0+c] for i in block bi, j in block
-// bj (16-row blocks), j <= i.  Lane l loads the 16-byte segment
-// c = 4(l/16) .. 4(l/16)+3 of rows 16 bi + l%16 (A) and 16 bj + l%16 (B);
-// instruction q multiplies component q, so the four v_mfma_f32_16x16x4_f32
-// cover c = 0..15.  Register r of lane l holds row 4(l/16) + r, column l%16.
-// Rows at or beyond N read row N-1 and their results are dropped.
-template <class MF>
-QPD void rank16_tile16(MF *M, int N, int npos, int p0, int bi, int bj) {
-  typedef typename Vec4<const MF>::type CV4;
-  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-  const int ia = min(16 * bi + c16, N - 1), jb = min(16 * bj + c16, N - 1);
-  const f4v a = *reinterpret_cast<CV4 *>(M + moff(ia) + p0 + 4 * g);
-  f4v b = *reinterpret_cast<CV4 *>(M + moff(jb) + p0 + 4 * g);
-  const int c0 = p0 + 4 * g;
-  b.x *= c0 + 0 < npos ? 1.f : -1.f;
-  b.y *= c0 + 1 < npos ? 1.f : -1.f;
-  b.z *= c0 + 2 < npos ? 1.f : -1.f;
-  b.w *= c0 + 3 < npos ? 1.f : -1.f;
-  f4v acc = {0.f, 0.f, 0.f, 0.f};
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc, 0, 0, 0);
-  const int j = 16 * bj + c16;
+// ---------------------------------------------------------------------------
+// Panels of the factorisation, one wave at a time.
+//
+// A wave works on four 16-row blocks ("slots") of one 16-column panel: first
+// as 16x16 tiles in the matrix cores' result layout with rows and columns
+// swapped (lane 16 g + c holds row c, columns 4g .. 4g+3 of its block, so a
+// tile is one 16-byte load or store per lane), then, for the elimination,
+// with a row per lane (lane 16 s + c holds all 16 columns of row c of slot
+// s).
+
+// (a, b) <- rows of lanes exchanged: the upper half (odd 16-lane rows) of a
+// with the lower half (even rows) of b.
+QPD void swap32(float &a, float &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+  a = __int_as_float(r[0]); b = __int_as_float(r[1]);
+}
+QPD void swap16(float &a, float &b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+  a = __int_as_float(r[0]); b = __int_as_float(r[1]);
+}
+// Tile layout of four slots -> a row per lane: the 4x4 transposition between
+// slot index (register) and column group (16-lane row), register by register.
+QPD void tiles_to_rows(const f4v (&t)[4], float (&P)[kNB]) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = 16 * bi + 4 * g + r;
-    if (i < N && j <= i) M[moff(i) + j] -= acc[r];
+    float x0 = t[0][r], x1 = t[1][r], x2 = t[2][r], x3 = t[3][r];
+    swap32(x0, x2);
+    swap32(x1, x3);
+    swap16(x0, x1);
+    swap16(x2, x3);
+    P[r] = x0; P[4 + r] = x1; P[8 + r] = x2; P[12 + r] = x3;
   }
 }
 
-// One row's 16-column panel segment M[i][k0 .. k0+15] into registers (zeros
-// for rows at or beyond N), and back with exact zeros right of the diagonal
-// (r = i - k0 is the row's position in the panel).
-template <class MF>
-QPD void panel_load(const MF *M, int N, int k0, int i, float (&R)[kNB]) {
+// Tiles t[0 .. CNT-1] -= sum over panels k < np of L[block, k] sg L[panel, k]':
+// ra[u] and rb point at this lane's row of block u and of the panel's diagonal
+// block (+ 4g), whose 16-byte segment of panel k is 16 k floats further on.
+// Instruction q multiplies component q, so the four v_mfma_f32_16x16x4_f32
+// cover the 16 columns; each panel's sum is formed from zero and then
+// subtracted, in ascending order of k.  The segments of the next panel are
+// loaded while this one's products run.
+template <int CNT, class MF>
+QPD void update_tiles(const MF *const (&ra)[4], const MF *rb, int np, int npos, f4v (&t)[4]) {
   typedef typename Vec4<const MF>::type CV4;
-  const bool in = i < N;
-  const MF *row = M + moff(min(i, N - 1)) + k0;
+  const int g4 = 4 * ((threadIdx.x & 63) >> 4);
+  f4v a[CNT], b = *reinterpret_cast<CV4 *>(rb);
 #pragma unroll
-  for (int c = 0; c < kNB; c += 4) {
-    const f4v v4 = *reinterpret_cast<CV4 *>(row + c);
-    R[c] = in ? v4.x : 0.f;
-    R[c + 1] = in ? v4.y : 0.f;
-    R[c + 2] = in ? v4.z : 0.f;
-    R[c + 3] = in ? v4.w : 0.f;
-  }
-}
-template <class MF>
-QPD void panel_store(MF *M, int N, int k0, int i, const float (&R)[kNB], float &lmax) {
-  typedef typename Vec4<MF>::type V4;
-  if (i >= N) return;
-  const int r = i - k0;
-  MF *row = M + moff(i) + k0;
+  for (int u = 0; u < CNT; ++u) a[u] = *reinterpret_cast<CV4 *>(ra[u]);
+#pragma unroll 2
+  for (int k = 0; k < np; ++k) {
+    const int kn = 16 * min(k + 1, np - 1);
+    f4v an[CNT];
+    const f4v bn = *reinterpret_cast<CV4 *>(rb + kn);
 #pragma unroll
-  for (int c = 0; c < kNB; c += 4) {
-    f4v v4;
-    v4.x = (c + 0 <= r) ? R[c + 0] : 0.f;
-    v4.y = (c + 1 <= r) ? R[c + 1] : 0.f;
-    v4.z = (c + 2 <= r) ? R[c + 2] : 0.f;
-    v4.w = (c + 3 <= r) ? R[c + 3] : 0.f;
-    *reinterpret_cast<V4 *>(row + c) = v4;
-    // largest |L| written (a NaN counts as infinite)
-    const float a = fmaxf(fmaxf(fabsf(v4.x), fabsf(v4.y)), fmaxf(fabsf(v4.z), fabsf(v4.w)));
-    const bool nan = v4.x != v4.x || v4.y != v4.y || v4.z != v4.z || v4.w != v4.w;
-    lmax = nan ? __int_as_float(0x7f800000) : fmaxf(lmax, a);
+    for (int u = 0; u < CNT; ++u) an[u] = *reinterpret_cast<CV4 *>(ra[u] + kn);
+    if (16 * k + kNB > npos) {  // some columns of the panel have sign -1
+      const int c0 = 16 * k + g4;
+      b.x *= c0 + 0 < npos ? 1.f : -1.f;
+      b.y *= c0 + 1 < npos ? 1.f : -1.f;
+      b.z *= c0 + 2 < npos ? 1.f : -1.f;
+      b.w *= c0 + 3 < npos ? 1.f : -1.f;
+    }
+    f4v acc[CNT];
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) acc[u] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < CNT; ++u)
+        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q], a[u][q], acc[u], 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) t[u] -= acc[u];
+    b = bn;
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) a[u] = an[u];
   }
 }
 
-// Factor the 16-column panel starting at k0 (rows k0..N-1) by one wave in
-// registers (lane = row, readlane broadcasts); writes L back with exact
-// zeros right of the diagonal.  Rows are taken 64 at a time: chunk 0 holds
-// the diagonal block, and up to four more chunks are eliminated in the same
-// sweep; any further chunks (more than 320 rows) replay the eliminations
-// with the finished diagonal block, so registers stay bounded for any N.
-// Returns true if a pivot failed.
-//
 // Dynamic regularisation (dyn): a pivot sg*a_jj that is not above
 // kPivTol * pmax, with pmax the largest pivot accepted so far in its block
 // (the H block, or the border from its first column on), is taken as
@@ -542,131 +542,97 @@ constexpr float kPivTol = 1e-6f;
 constexpr float kPivReg = 1e-5f;
 constexpr float kGrowthMax = 1e2f;  // accepted max|L| / sqrt(largest pivot) with
                                     // replacements (a stable factor stays near 1)
-// The panel's first sweep with G extra 64-row chunks in registers (rows
-// k0 + lane + 64 (1 + g)); gact (uniform) counts those that hold rows of
-// the system, and without any (gact = 0: chunks entirely past row N-1 would
-// only carry zeros) a scalar branch per column skips their updates.  P0 holds chunk 0 (the diagonal
-// block) on return and iv the signed pivot inverses, for the replay of any
-// further chunks.  The multipliers of column jj are read from
-// ps = a[.][jj] / L[jj][jj], which equals L[.][jj] sg_jj exactly (the sign
-// is folded into the broadcast source instead of into every multiplier).
-template <int G, class MF>
-QPD bool panel_sweep(MF *M, int N, int npos, int k0, int kb, int gact, bool dyn, float &pmax,
-                     float &pmaxh, int &nreg, float &lmax, float (&P0)[kNB], float (&iv)[kNB]) {
+
+// Eliminate one panel of kb columns from k0 on in a wave's registers (a row
+// per lane); lanes 0 .. 15 hold the diagonal block, so that every multiplier
+// and pivot is one lane broadcast away.  The border's pivots (its Schur
+// complement, of order |C_j|^2 / |H| plus the diagonal Dl, with the rows
+// equilibrated: border_exponent) are tested against the border's own largest
+// pivot: at the first border column the running maximum restarts (the H
+// block's is kept in pmaxh).  The multipliers of column jj are read from
+// ps = a[.][jj] / L[jj][jj], which equals L[.][jj] sg_jj exactly.
+//
+// The chain from one pivot to the next bounds the factorisation of every
+// size, so the common form (CHECKED false: kb = 16) carries no decisions:
+// every pivot is taken as good, and the return value says whether one was
+// not (not above kPivTol * pmax, or not finite), in which case the caller
+// repeats the panel from its saved tiles with CHECKED, which decides pivot by
+// pivot and returns whether one failed.  Without the decisions' branches
+// between the columns a panel takes 2.1K cycles, with them 5.7K (measured
+// alone on a CU).
+template <bool CHECKED>
+QPD bool eliminate(float (&P)[kNB], float (&iv)[kNB], int k0, int kb, int npos, bool dyn,
+                   float &pmax, float &pmaxh, int &nreg) {
   const int lane = threadIdx.x & 63;
-  float P[G > 0 ? G : 1][kNB];
-  panel_load(M, N, k0, k0 + lane, P0);
-#pragma unroll
-  for (int g = 0; g < G; ++g) panel_load(M, N, k0, k0 + lane + 64 * (1 + g), P[g]);
-  bool fail = false;
+  bool flag = false;
 #pragma unroll
   for (int jj = 0; jj < kNB; ++jj) {
-    iv[jj] = 0.f;
-    if (jj < kb) {
-      // row k0+jj is in lane jj of chunk 0
+    if (!CHECKED || jj < kb) {
       const float sg = (k0 + jj) < npos ? 1.f : -1.f;
-      // the border's pivots (its Schur complement, of order |C_j|^2 / |H|
-      // plus the diagonal Dl, with the rows equilibrated: border_exponent)
-      // are tested against the border's own largest pivot: at the first
-      // border column the running maximum restarts (the H block's is kept
-      // in pmaxh)
       if (k0 + jj == npos) {
         pmaxh = pmax;
         pmax = 0.f;
       }
-      float tt = sg * readlane(P0[jj], jj);
-      if (dyn && !(tt > kPivTol * pmax) && tt >= -FLT_MAX && pmax > 0.f) {
-        tt = kPivReg * pmax;
-        ++nreg;
-      }
-      const bool ok = tt > 0.f && tt <= FLT_MAX;
-      if (ok) pmax = fmaxf(pmax, tt);
-      fail |= !ok;
-      // pivot sqrt(tt) and its signed inverse from one hardware reciprocal
-      // square root (about 1 ulp): this chain is on the panel's critical path
-      const float rs = ok ? __builtin_amdgcn_rsqf(tt) : 1.f;
-      const float d = ok ? tt * rs : 1.f;
-      const float inv = sg * rs;
-      iv[jj] = inv;
-      const float ps = P0[jj] * rs;  // L[k0+lane][k0+jj] sg below the diagonal
-      P0[jj] = lane > jj ? ps * sg : (lane == jj ? d : P0[jj]);
-      if constexpr (G <= 1) {
-        // the multipliers first, into scalar registers, then the updates:
-        // the broadcasts issue back to back instead of each waiting on the
-        // last one's result
-        float lc[kNB];
-#pragma unroll
-        for (int cc = jj + 1; cc < kNB; ++cc) lc[cc] = readlane(ps, cc);  // L[k0+cc][k0+jj] sg
-#pragma unroll
-        for (int cc = jj + 1; cc < kNB; ++cc) P0[cc] = fmaf(-P0[jj], lc[cc], P0[cc]);
-        if (G == 1) {  // (zeros past row N-1: a branch on gact costs more)
-          P[0][jj] *= inv;
-#pragma unroll
-          for (int cc = jj + 1; cc < kNB; ++cc) P[0][cc] = fmaf(-P[0][jj], lc[cc], P[0][cc]);
+      float tt = sg * readlane(P[jj], jj), rs, d;
+      if constexpr (CHECKED) {
+        if (dyn && !(tt > kPivTol * pmax) && tt >= -FLT_MAX && pmax > 0.f) {
+          tt = kPivReg * pmax;
+          ++nreg;
         }
-      } else if (gact > 0) {
-        // more chunks: one multiplier at a time (fewer scalar registers live)
-#pragma unroll
-        for (int g = 0; g < G; ++g) P[g][jj] *= inv;
-#pragma unroll
-        for (int cc = jj + 1; cc < kNB; ++cc) {
-          const float lc = readlane(ps, cc);  // L[k0+cc][k0+jj] sg
-          P0[cc] = fmaf(-P0[jj], lc, P0[cc]);
-#pragma unroll
-          for (int g = 0; g < G; ++g) P[g][cc] = fmaf(-P[g][jj], lc, P[g][cc]);
-        }
+        const bool ok = tt > 0.f && tt <= FLT_MAX;
+        if (ok) pmax = fmaxf(pmax, tt);
+        flag |= !ok;
+        // pivot sqrt(tt) and its signed inverse from one hardware reciprocal
+        // square root (about 1 ulp)
+        rs = ok ? __builtin_amdgcn_rsqf(tt) : 1.f;
+        d = ok ? tt * rs : 1.f;
       } else {
-#pragma unroll
-        for (int cc = jj + 1; cc < kNB; ++cc) P0[cc] = fmaf(-P0[jj], readlane(ps, cc), P0[cc]);
+        flag |= !(tt > kPivTol * pmax && tt <= FLT_MAX);
+        pmax = fmaxf(pmax, tt);
+        rs = __builtin_amdgcn_rsqf(tt);
+        d = tt * rs;
       }
+      iv[jj] = sg * rs;
+      const float ps = P[jj] * rs;  // L sg below the diagonal
+      const float nl = ps * -sg;
+      P[jj] = lane == jj ? d : -nl;
+      // the multipliers first, into scalar registers, then the updates: the
+      // broadcasts issue back to back instead of each waiting on the last
+      // one's result
+      float lc[kNB];
+#pragma unroll
+      for (int cc = jj + 1; cc < kNB; ++cc) lc[cc] = readlane(ps, cc);
+#pragma unroll
+      for (int cc = jj + 1; cc < kNB; ++cc) P[cc] = fmaf(lc[cc], nl, P[cc]);
     }
   }
-  panel_store(M, N, k0, k0 + lane, P0, lmax);
-  if (gact > 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) panel_store(M, N, k0, k0 + lane + 64 * (1 + g), P[g], lmax);
-  }
-  return fail;
+  return flag;
 }
 
-// The panel factorisation (see above).
-template <int RPL, class MF>
-QPD bool factor_panel(MF *M, int N, int npos, int k0, bool dyn, float &pmax, float &pmaxh,
-                      int &nreg, float &lmax) {
-  constexpr int GRP = RPL - 1 < 4 ? RPL - 1 : 4;
-  const int lane = threadIdx.x & 63;
-  const int kb = min(kNB, N - k0);
-  float P0[kNB], iv[kNB];
-  // extra chunks that hold rows of the system (uniform)
-  const int gact = min(GRP, (N - k0 - 1) >> 6);
-  const bool fail =
-      panel_sweep<GRP>(M, N, npos, k0, kb, gact, dyn, pmax, pmaxh, nreg, lmax, P0, iv);
-  // rows past the first 64 (1 + GRP): replay the eliminations with the
-  // finished diagonal block, GRP chunks at a time
-  float P[GRP > 0 ? GRP : 1][kNB];
-#pragma unroll 1
-  for (int t0 = 1 + GRP; t0 < RPL; t0 += GRP) {
-    if (k0 + 64 * t0 >= N) break;
+// The same eliminations on 64 further rows, with the diagonal block D (lanes
+// 0 .. 15, finished) and the signed pivot inverses of eliminate().
+QPD void eliminate_more(float (&P)[kNB], const float (&D)[kNB], const float (&iv)[kNB], int k0,
+                        int kb, int npos) {
 #pragma unroll
-    for (int g = 0; g < GRP; ++g) panel_load(M, N, k0, k0 + lane + 64 * (t0 + g), P[g]);
+  for (int jj = 0; jj < kNB; ++jj) {
+    if (jj < kb) {
+      const float sg = (k0 + jj) < npos ? 1.f : -1.f;
+      P[jj] *= iv[jj];
 #pragma unroll
-    for (int jj = 0; jj < kNB; ++jj) {
-      if (jj < kb) {
-        const float sg = (k0 + jj) < npos ? 1.f : -1.f;
-#pragma unroll
-        for (int g = 0; g < GRP; ++g) P[g][jj] *= iv[jj];
-#pragma unroll
-        for (int cc = jj + 1; cc < kNB; ++cc) {
-          const float lc = readlane(P0[jj], cc) * sg;
-#pragma unroll
-          for (int g = 0; g < GRP; ++g) P[g][cc] = fmaf(-P[g][jj], lc, P[g][cc]);
-        }
-      }
+      for (int cc = jj + 1; cc < kNB; ++cc)
+        P[cc] = fmaf(-P[jj], readlane(D[jj], cc) * sg, P[cc]);
     }
-#pragma unroll
-    for (int g = 0; g < GRP; ++g) panel_store(M, N, k0, k0 + lane + 64 * (t0 + g), P[g], lmax);
   }
-  return fail;
+}
+
+// Row i's 16-column panel segment from registers.
+template <class MF>
+QPD void store_row(MF *M, int i, int k0, const float (&P)[kNB]) {
+  typedef typename Vec4<MF>::type V4;
+  MF *row = M + moff(i) + k0;
+#pragma unroll
+  for (int c = 0; c < kNB; c += 4)
+    *reinterpret_cast<V4 *>(row + c) = f4v{P[c], P[c + 1], P[c + 2], P[c + 3]};
 }
 
 // Equilibration of the border for the pivot tests.  The regularisation
@@ -736,96 +702,176 @@ QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
 }
 
 // In-place M = L diag(sg) L' (lower triangle, packed-blocked layout),
-// sg_j = +1 for j < npos, -1 otherwise.  Blocked right-looking with one
-// panel of lookahead: after panel k is factored, all waves first apply it
-// to the next panel's 16 columns; then wave 0 factors the next panel while
-// the other waves apply panel k to the rest of the trailing matrix.  The
-// updates run on the matrix cores in 16x16 tiles (rank16_tile16).  The
-// strict upper part of each row's last 16-column segment is left at exact
-// zeros.  Returns false (uniformly) if a pivot sg_j * a_jj is not a positive
-// finite number.  With dyn, numerically zero pivots are regularised (see
-// factor_panel; the tests see the border equilibrated, border_exponent) and
-// flag[2] receives their count.  flag[0] is the failure flag, flag[4] the
-// largest accepted pivot (float bits, the border's in equilibrated units);
-// flag[1] and flag[3] are left alone, flag[8 ..] is scratch.  RPL = rows
-// per lane, >= ceil(N / 64).
+// sg_j = +1 for j < npos, -1 otherwise.  Left-looking in panels of 16 columns:
+// the panel's 16-row blocks are dealt to the waves (block j below the
+// diagonal block to wave j mod T/64), each wave subtracts the products of all
+// earlier panels from its blocks in registers (update_tiles), wave 0 passes
+// the updated diagonal block on through `dsh`, and each wave eliminates the
+// panel on the diagonal block and its own rows (eliminate), so that an
+// element of M is read once and written once, and two barriers separate the
+// panels.  A right-looking form reads and writes the trailing matrix once
+// per panel: with the factor in global memory, one tile in flight per wave,
+// that traffic bounded it (64 QPs of n = 256, forward and backward: 56.5 ->
+// 25.6 ms; 1024 of n = 100: 18.5 -> 11.8 ms).
+// The strict upper part of each row's last 16-column segment is left at
+// exact zeros.  Returns false (uniformly) if a pivot sg_j * a_jj is not a
+// positive finite number.  With dyn, numerically zero pivots are regularised
+// (see kPivTol; the tests see the border equilibrated, border_exponent) and
+// flag[2] receives their count.  flag[4] is the largest accepted pivot (float
+// bits, the border's in equilibrated units); flag[0] is scratch, as are
+// flag[8 ..]; flag[1] and flag[3] are left alone.  RPL = rows per lane,
+// >= ceil(N / 64).
 template <int T, int RPL, class MF>
-QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn) {
-  M = rflp(M); N = rfl(N); npos = rfl(npos); flag = rflp(flag); dyn = rfl(dyn);
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  // wave 0's running pivot scale and count of regularised pivots
-  float pmax = 0.f, pmaxh = 0.f, lmax = 0.f;
-  int nreg = 0;
-  if (tid == 0) { flag[0] = 0; flag[2] = 0; }
+QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *dsh) {
+  M = rflp(M); N = rfl(N); npos = rfl(npos); flag = rflp(flag); dyn = rfl(dyn); dsh = rflp(dsh);
+  constexpr int NW = T / 64;
+  constexpr int kMaxBlk = 4 * RPL;            // 16-row blocks of the largest system
+  constexpr bool kMore = kMaxBlk > 3 * NW + 1;  // blocks beyond the waves' first slots
+  constexpr int DS = 2 * T >= 320 ? 20 : 16;  // row stride of dsh (2 T floats)
+  typedef typename Vec4<const MF>::type CV4;
+  const int tid = threadIdx.x, lane = tid & 63, wid = rfl(tid >> 6);
+  const int c16 = lane & 15, sl = lane >> 4, g4 = 4 * sl;
+  const int nblk = (N + 15) >> 4;
+  float pmax = 0.f, pmaxh = 0.f;  // running pivot scale and count of regularised
+  int nreg = 0;                   // pivots: the same in every wave that has rows
+  bool fail = false;
   // with the pivot tests on, they see the border equilibrated: wave 0
-  // scales the rows before its first panel (the other waves first read
-  // them after the barrier that follows it) and takes the scaling back out
-  // of the factor at the end (see border_exponent)
+  // scales the rows first and takes the scaling back out of the factor at
+  // the end (see border_exponent)
   const bool eq = dyn && N > npos;
   const int emax = eq ? border_emax<T>(flag) : 0;
-  if (wid == 0) {
-    if (eq) {
+  if (eq) {
+    if (wid == 0) {
       border_shifted_rows(M, N, npos, emax, [&](int i, int sh) {
         MF *row = M + moff(i);
         const float s = ldexpf(1.f, sh);
         for (int j = lane; j < npos; j += 64) row[j] *= s;
         if (lane == 0) row[i] *= s * s;  // the border block is diagonal here
       });
-      __threadfence_block();  // the panel's loads see the scaled rows
-    }
-    const bool fail = factor_panel<RPL>(M, N, npos, 0, dyn, pmax, pmaxh, nreg, lmax);
-    if (fail && lane == 0) flag[0] = 1;
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int k0 = 0; k0 + kNB < N; k0 += kNB) {
-    const int r0 = k0 + kNB, R = N - r0;
-    // (1) apply panel k0 to the next panel's columns [r0, r0+16): 16x16
-    // tiles on the matrix cores, one wave per tile
-    {
-      const int nbl = (R + 15) >> 4;
-      for (int t = wid; t < nbl; t += T / 64) rank16_tile16(M, N, npos, k0, (r0 >> 4) + t, r0 >> 4);
     }
     __syncthreads();
-    // (2) wave 0: factor the next panel; waves 1..: rest of the update
-    if (wid == 0) {
-      const bool fail = factor_panel<RPL>(M, N, npos, r0, dyn, pmax, pmaxh, nreg, lmax);
-      if (fail && lane == 0) flag[0] = 1;
-    } else {
-      const int r1 = r0 + kNB, R1 = N - r1;
-      if (R1 > 0) {
-        const int nbl = (R1 + 15) >> 4;
-        const int ntiles = nbl * (nbl + 1) / 2;
-        for (int t = wid - 1; t < ntiles; t += T / 64 - 1) {
-          int ti, tj;
-          tile_ij(t, ti, tj);
-          rank16_tile16(M, N, npos, k0, (r1 >> 4) + ti, (r1 >> 4) + tj);
+  }
+#pragma unroll 1
+  for (int p = 0; p < nblk; ++p) {
+    const int k0 = kNB * p, kb = min(kNB, N - k0), below = nblk - 1 - p;
+    // this lane's row of block q (clamped: rows past N-1 read row N-1 and are
+    // not stored)
+    auto row_of = [&](int q) -> const MF * {
+      const int r = min(c16, N - 1 - kNB * q);
+      return M + (moff(kNB * q) + r * (20 + kNB * q) + g4);
+    };
+    const MF *rb = row_of(p);
+    // slots of this wave: block p + j(s); wave 0's slot 0 is the diagonal
+    // block, which the other waves get through dsh
+    const int s0 = wid == 0 ? 0 : 1;
+    auto block_of = [&](int s) { return wid == 0 ? NW * s : wid + NW * (s - 1); };
+    // the updated tiles, slots s0 .. of this wave
+    f4v t[4];
+    auto update = [&](auto cnt, auto first) {
+      constexpr int CNT = decltype(cnt)::value;
+      const MF *ra[4];
+#pragma unroll
+      for (int u = 0; u < CNT; ++u) {
+        ra[u] = row_of(p + first(u));
+        t[u] = *reinterpret_cast<CV4 *>(ra[u] + k0);
+      }
+      if (p) update_tiles<CNT>(ra, rb, p, npos, t);
+    };
+    auto update_n = [&](int cnt, auto first) {
+      if (cnt == 1) update(std::integral_constant<int, 1>{}, first);
+      if constexpr (kMaxBlk > NW)
+        if (cnt == 2) update(std::integral_constant<int, 2>{}, first);
+      if constexpr (kMaxBlk > 2 * NW)
+        if (cnt == 3) update(std::integral_constant<int, 3>{}, first);
+      if constexpr (kMaxBlk > 3 * NW)
+        if (cnt == 4) update(std::integral_constant<int, 4>{}, first);
+    };
+    const f4v zero = {0.f, 0.f, 0.f, 0.f};
+    t[0] = t[1] = t[2] = t[3] = zero;
+    // slots in use: j(s) <= below
+    const int used = wid == 0 ? 1 + min(3, below / NW) : (wid <= below ? min(3, (below - wid) / NW + 1) : 0);
+    update_n(used, [&](int u) { return block_of(u + s0); });
+    if (wid == 0) *reinterpret_cast<lf4 *>(dsh + c16 * DS + g4) = t[0];
+    __syncthreads();
+    if (used) {
+      if (wid != 0) {
+        t[3] = t[2]; t[2] = t[1]; t[1] = t[0];
+        t[0] = *reinterpret_cast<const lf4 *>(dsh + c16 * DS + g4);
+      }
+      float P[kNB], iv[kNB];
+      tiles_to_rows(t, P);
+      bool again = true;
+      if (kb == kNB) {
+        const float pm = pmax, ph = pmaxh;
+        again = __any(eliminate<false>(P, iv, k0, kNB, npos, dyn, pmax, pmaxh, nreg));
+        if (again) {
+          pmax = pm;
+          pmaxh = ph;
+          tiles_to_rows(t, P);
+        }
+      }
+      if (again) fail |= eliminate<true>(P, iv, k0, kb, npos, dyn, pmax, pmaxh, nreg);
+      if (wid == 0) {
+#pragma unroll
+        for (int c = 1; c < kNB; ++c) P[c] = lane < c ? 0.f : P[c];  // right of the diagonal
+      }
+      {
+        const int j = block_of(sl), i = kNB * (p + j) + c16;
+        if ((wid == 0 || sl > 0) && j <= below && i < N) store_row(M, i, k0, P);
+      }
+      if constexpr (kMore) {
+        // blocks past the waves' first slots, four per wave at a time
+#pragma unroll 1
+        for (int j0 = 3 * NW + 1 + wid; j0 <= below; j0 += 4 * NW) {
+          t[0] = t[1] = t[2] = t[3] = zero;
+          update_n(min(4, (below - j0) / NW + 1), [&](int u) { return j0 + NW * u; });
+          float R[kNB];
+          tiles_to_rows(t, R);
+          eliminate_more(R, P, iv, k0, kb, npos);
+          const int j = j0 + NW * sl, i = kNB * (p + j) + c16;
+          if (j <= below && i < N) store_row(M, i, k0, R);
         }
       }
     }
     __syncthreads();
   }
-  if (wid == 0) {
-    lmax = wave_bfly<OpMax>(lmax);
+  pmax = fmaxf(pmax, pmaxh);
+  if (tid == 0) {
+    flag[0] = fail;
+    flag[2] = nreg;
+    flag[4] = __float_as_int(pmax);  // largest accepted pivot (retry scale)
+  }
+  __syncthreads();
+  bool good = flag[0] == 0;
+  if (flag[2] > 0) {
     // with regularised pivots, entries of L far beyond the scale sqrt(pmax)
     // of a stable factor mean the replaced pivots amplified rounding errors:
     // report a failure so the caller factors again with a uniform floor
-    pmax = fmaxf(pmax, pmaxh);
-    if (lane == 0 && nreg > 0 && !(lmax <= kGrowthMax * sqrtf(pmax))) flag[0] = 1;
-    if (eq) {
+    float lmax = 0.f;
+    for (int i = wid; i < N; i += NW) {
+      const MF *row = M + moff(i);
+      for (int j = lane; j <= i; j += 64) {
+        const float v = fabsf(row[j]);
+        lmax = v <= FLT_MAX ? fmaxf(lmax, v) : __int_as_float(0x7f800000);
+      }
+    }
+    lmax = wave_bfly<OpMax>(lmax);
+    if (lane == 0) flag[8 + wid] = __float_as_int(lmax);
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) lmax = fmaxf(lmax, __int_as_float(flag[8 + w]));
+    if (!(lmax <= kGrowthMax * sqrtf(__int_as_float(flag[4])))) good = false;
+  }
+  if (eq) {
+    if (wid == 0) {
       border_shifted_rows(M, N, npos, emax, [&](int i, int sh) {
         MF *row = M + moff(i);
         const float r = ldexpf(1.f, -sh);
         for (int j = lane; j <= i; j += 64) row[j] *= r;
       });
     }
+    __syncthreads();
   }
-  if (tid == 0) {
-    flag[2] = nreg;
-    flag[4] = __float_as_int(pmax);  // largest accepted pivot (retry scale)
-  }
-  __syncthreads();
-  return flag[0] == 0;
+  return good;
 }
 
 // dv[c] = dinv[c] for c < CW (CW a multiple of 4) as 16-byte loads; dinv
@@ -1919,7 +1965,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     border_delta<T>(C, nb, delta_rel, 0.f);
   }
   QPK_PT(C, PH_ASM);
-  bool ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, C.dyn != 0);
+  bool ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, C.dyn != 0, C.part);
   QPK_PT(C, PH_FACT);
   *regularised = delta_rel > 0.f || floor || C.iflag[2] > 0;
   if (!ok && C.dyn) {
@@ -1928,7 +1974,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     const float pmax = __int_as_float(C.iflag[4]);
     assemble<T>(C, nb, ne, wts, true, 0.f);
     border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * pmax);
-    ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, true);
+    ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, true, C.part);
     *regularised = true;
   }
   return ok;
@@ -2069,7 +2115,7 @@ QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
   const int ne = compact_rows<T>(C.role, m, C.elist, C.red);
   assemble<T>(C, 0, ne, C.E, false, 0.f);
   const int N = n + p;
-  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, dyn);
+  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, dyn, C.part);
   make_dinv<T>(C, N);
   if (m) {
     const lf *hv[1] = {C.h};
@@ -2269,7 +2315,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
   __syncthreads();
   const int N = n + p;
   assemble<T>(C, 0, ne, C.E, false, delta_reg);
-  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false);
+  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false, C.part);
   const double dn = n, dm = m, dp = p, dN = N;
   work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;
   work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0;
@@ -2549,7 +2595,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     for (int i = tid; i < m; i += T) C.dv0[i] = C.E[i] * (C.dv0[i] + (gz ? gz[i] : 0.f));
   } else {
     assemble<T>(C, nb, ne, C.t1, false, 0.f);
-    ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false);
+    ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false, C.part);
     const int nref = plain_refine_steps(C.rmode, refine_steps, 2);
     work += wfac + nref * wstep;
     if (!ok) return kAdjFactorFail;
