@@ -48,7 +48,7 @@ struct Params {
   // serving
   const struct SlotDesc *desc;
   int32_t mode;
-  long long *phase;  // [B][16] phase cycle counters (profiling builds only)
+  long long *phase;  // [B][32] phase cycle counters (profiling builds only)
 };
 
 // One resident serving slot.  All pointers are device pointers into the
@@ -79,7 +79,11 @@ bool mfma_stage_fits(int n, int m, int p, int kb, bool m_in_lds, int threads);
 // LDS of a CU, the kernels' static LDS (context table, profiling counters;
 // an upper bound) and the most dynamic LDS one QP may take.
 constexpr size_t kCuLds = 160 * 1024;
+#ifdef QPK_PHASE_TIMING
+constexpr size_t kStaticLds = 512 + 256;
+#else
 constexpr size_t kStaticLds = 512;
+#endif
 size_t lds_limit();
 // Allocation-free workspace (qp_noalloc.hip): resolve the current device's
 // copy of the fixed scratch array (once per device), and look it up.

@@ -90,6 +90,23 @@ template <class F> struct Vec2;
 template <> struct Vec2<lf> { typedef const __attribute__((address_space(3))) f2v type; };
 template <> struct Vec2<gf> { typedef const __attribute__((address_space(1))) f2v type; };
 
+// The thread's index and a uniform size, as values the compiler cannot trace
+// back.  The Newton loop inlines every phase; known as loop invariants, each
+// phase's lane predicates, row addresses and trip counts would be computed
+// before the loop and kept (spilled) for all of it: 152 bytes of scratch per
+// lane and 399 scalar spills in the solve kernel of 256 threads and 2 rows per
+// lane, none and 304 with the index opaque (1024 QPs of n = 100, forward and
+// backward: 12.0 -> 10.7 ms).
+QPD int tidx() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+QPD int opaque(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 QPD bool finitef(float a) { return fabsf(a) <= FLT_MAX; }
 
 QPD float readlane(float v, int lane) {
@@ -124,23 +141,26 @@ QPD void wave_sync() {
 }
 
 // Optional per-phase cycle counters for profiling builds (-DQPK_PHASE_TIMING):
-// thread 0 accumulates clock64() deltas per phase in LDS; the kernel writes
-// them to Params::phase.  Compiled out otherwise.
+// thread 0 accumulates clock64() deltas per phase in LDS (a workgroup barrier
+// at every mark); the kernel writes them to Params::phase.  Compiled out
+// otherwise.
+enum Phase { PH_INIT, PH_RESID, PH_PART, PH_ASM, PH_FACT, PH_RHS, PH_SOLVE, PH_REFINE,
+             PH_RECOVER, PH_STEP, PH_BWD, PH_OUT, PH_ASM_BORDER, PH_ASM_DIAG, PH_FACT_UPDATE,
+             PH_FACT_ELIM, PH_DINV, PH_MATVEC, PH_KAPPA, PH_AFFINE, PH_REFINE_APPLY, PH_N = 32 };
 #ifdef QPK_PHASE_TIMING
-#define QPK_PT(C, k)                                    \
+static __shared__ long long qpk_pt[PH_N];  // the last entry: the previous mark's clock
+#define QPK_PT(k)                                       \
   do {                                                  \
     __syncthreads();                                    \
     if (threadIdx.x == 0) {                             \
       const long long _t = clock64();                   \
-      (C).pt[k] += _t - (C).pt[15];                     \
-      (C).pt[15] = _t;                                  \
+      qpk_pt[k] += _t - qpk_pt[PH_N - 1];               \
+      qpk_pt[PH_N - 1] = _t;                            \
     }                                                   \
   } while (0)
 #else
-#define QPK_PT(C, k) ((void)0)
+#define QPK_PT(k) ((void)0)
 #endif
-enum Phase { PH_INIT, PH_RESID, PH_PART, PH_ASM, PH_FACT, PH_RHS, PH_SOLVE, PH_REFINE,
-             PH_RECOVER, PH_STEP, PH_BWD, PH_OUT, PH_N = 16 };
 
 struct OpSum { template <class V> QPD static V f(V a, V b) { return a + b; } };
 struct OpMax { QPD static float f(float a, float b) { return fmaxf(a, b); } };
@@ -224,8 +244,8 @@ QPD void block_reduce(float (&v)[K], lf *red) {
     v[k] = wave_bfly<Op>(v[k]);
   }
   if constexpr (T > 64) {
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
+    const int w = tidx() >> 6;
+    if ((tidx() & 63) == 0) {
 #pragma unroll
       for (int k = 0; k < K; ++k) red[w * K + k] = v[k];
     }
@@ -355,7 +375,7 @@ QPD void load_row4(const RF *R, int ld, int rows, int cols, int i, int jb, int s
 template <int T, int NV, class RF>
 QPD void rowdot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV],
                 lf *const (&out)[NV]) {
-  const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int sub = tidx() & 15, grp = tidx() >> 4;
   for (int jb = 0; jb < cols; jb += 64) {
     float xv[NV][4];
 #pragma unroll
@@ -400,7 +420,7 @@ template <int T, int NV, class RF>
 QPD void coldot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV],
                 lf *const (&out)[NV], lf *part) {
   static_assert(NV <= 2, "part holds two floats per thread");
-  const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4, wid = tid >> 6;
+  const int tid = tidx(), sub = tid & 15, grp = tid >> 4, wid = tid >> 6;
   for (int jb = 0; jb < cols; jb += 64) {
     float c[NV][4];
 #pragma unroll
@@ -496,37 +516,49 @@ QPD void tiles_to_rows(const f4v (&t)[4], float (&P)[kNB]) {
 template <int CNT, class MF>
 QPD void update_tiles(const MF *const (&ra)[4], const MF *rb, int np, int npos, f4v (&t)[4]) {
   typedef typename Vec4<const MF>::type CV4;
-  const int g4 = 4 * ((threadIdx.x & 63) >> 4);
-  f4v a[CNT], b = *reinterpret_cast<CV4 *>(rb);
+  const int g4 = 4 * ((tidx() & 63) >> 4);
+  constexpr int U = CNT == 1 ? 2 : 1;  // panels per step: two independent chains at least
+  f4v a[U][CNT], b[U];
+  auto load = [&](int k, int h) {
+    const int o = 16 * min(k, np - 1);
+    b[h] = *reinterpret_cast<CV4 *>(rb + o);
 #pragma unroll
-  for (int u = 0; u < CNT; ++u) a[u] = *reinterpret_cast<CV4 *>(ra[u]);
-#pragma unroll 2
-  for (int k = 0; k < np; ++k) {
-    const int kn = 16 * min(k + 1, np - 1);
-    f4v an[CNT];
-    const f4v bn = *reinterpret_cast<CV4 *>(rb + kn);
+    for (int u = 0; u < CNT; ++u) a[h][u] = *reinterpret_cast<CV4 *>(ra[u] + o);
+  };
 #pragma unroll
-    for (int u = 0; u < CNT; ++u) an[u] = *reinterpret_cast<CV4 *>(ra[u] + kn);
-    if (16 * k + kNB > npos) {  // some columns of the panel have sign -1
-      const int c0 = 16 * k + g4;
-      b.x *= c0 + 0 < npos ? 1.f : -1.f;
-      b.y *= c0 + 1 < npos ? 1.f : -1.f;
-      b.z *= c0 + 2 < npos ? 1.f : -1.f;
-      b.w *= c0 + 3 < npos ? 1.f : -1.f;
+  for (int h = 0; h < U; ++h) load(h, h);
+#pragma unroll 1
+  for (int k = 0; k < np; k += U) {
+    f4v acc[U][CNT], bs[U], as[U][CNT];
+#pragma unroll
+    for (int h = 0; h < U; ++h) {
+      bs[h] = b[h];
+#pragma unroll
+      for (int u = 0; u < CNT; ++u) as[h][u] = a[h][u];
+      load(k + U + h, h);
+      if (16 * (k + h) + kNB > npos) {  // some columns of the panel have sign -1
+        const int c0 = 16 * (k + h) + g4;
+        bs[h].x *= c0 + 0 < npos ? 1.f : -1.f;
+        bs[h].y *= c0 + 1 < npos ? 1.f : -1.f;
+        bs[h].z *= c0 + 2 < npos ? 1.f : -1.f;
+        bs[h].w *= c0 + 3 < npos ? 1.f : -1.f;
+      }
+#pragma unroll
+      for (int u = 0; u < CNT; ++u) acc[h][u] = f4v{0.f, 0.f, 0.f, 0.f};
     }
-    f4v acc[CNT];
-#pragma unroll
-    for (int u = 0; u < CNT; ++u) acc[u] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int u = 0; u < CNT; ++u)
-        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q], a[u][q], acc[u], 0, 0, 0);
+      for (int h = 0; h < U; ++h)
 #pragma unroll
-    for (int u = 0; u < CNT; ++u) t[u] -= acc[u];
-    b = bn;
+        for (int u = 0; u < CNT; ++u)
+          acc[h][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bs[h][q], as[h][u][q], acc[h][u], 0, 0, 0);
 #pragma unroll
-    for (int u = 0; u < CNT; ++u) a[u] = an[u];
+    for (int h = 0; h < U; ++h)
+      if (k + h < np) {
+#pragma unroll
+        for (int u = 0; u < CNT; ++u) t[u] -= acc[h][u];
+      }
   }
 }
 
@@ -550,63 +582,127 @@ constexpr float kGrowthMax = 1e2f;  // accepted max|L| / sqrt(largest pivot) wit
 // equilibrated: border_exponent) are tested against the border's own largest
 // pivot: at the first border column the running maximum restarts (the H
 // block's is kept in pmaxh).  The multipliers of column jj are read from
-// ps = a[.][jj] / L[jj][jj], which equals L[.][jj] sg_jj exactly.
+// ps = a[.][jj] / L[jj][jj], which equals L[.][jj] sg_jj exactly.  iv
+// receives the signed pivot inverses.  Returns whether a pivot failed.
 //
-// The chain from one pivot to the next bounds the factorisation of every
-// size, so the common form (CHECKED false: kb = 16) carries no decisions:
-// every pivot is taken as good, and the return value says whether one was
-// not (not above kPivTol * pmax, or not finite), in which case the caller
-// repeats the panel from its saved tiles with CHECKED, which decides pivot by
-// pivot and returns whether one failed.  Without the decisions' branches
-// between the columns a panel takes 2.1K cycles, with them 5.7K (measured
-// alone on a CU).
-template <bool CHECKED>
-QPD bool eliminate(float (&P)[kNB], float (&iv)[kNB], int k0, int kb, int npos, bool dyn,
-                   float &pmax, float &pmaxh, int &nreg) {
-  const int lane = threadIdx.x & 63;
-  bool flag = false;
+// This form decides pivot by pivot; it runs only when eliminate() has found
+// a pivot that needs a decision.
+QPD bool eliminate_checked(float (&P)[kNB], float (&iv)[kNB], int k0, int kb, int npos, bool dyn,
+                           float &pmax, float &pmaxh, int &nreg) {
+  const int lane = tidx() & 63;
+  bool fail = false;
 #pragma unroll
   for (int jj = 0; jj < kNB; ++jj) {
-    if (!CHECKED || jj < kb) {
+    if (jj < kb) {
       const float sg = (k0 + jj) < npos ? 1.f : -1.f;
       if (k0 + jj == npos) {
         pmaxh = pmax;
         pmax = 0.f;
       }
-      float tt = sg * readlane(P[jj], jj), rs, d;
-      if constexpr (CHECKED) {
-        if (dyn && !(tt > kPivTol * pmax) && tt >= -FLT_MAX && pmax > 0.f) {
-          tt = kPivReg * pmax;
-          ++nreg;
-        }
-        const bool ok = tt > 0.f && tt <= FLT_MAX;
-        if (ok) pmax = fmaxf(pmax, tt);
-        flag |= !ok;
-        // pivot sqrt(tt) and its signed inverse from one hardware reciprocal
-        // square root (about 1 ulp)
-        rs = ok ? __builtin_amdgcn_rsqf(tt) : 1.f;
-        d = ok ? tt * rs : 1.f;
-      } else {
-        flag |= !(tt > kPivTol * pmax && tt <= FLT_MAX);
-        pmax = fmaxf(pmax, tt);
-        rs = __builtin_amdgcn_rsqf(tt);
-        d = tt * rs;
+      float tt = sg * readlane(P[jj], jj);
+      if (dyn && !(tt > kPivTol * pmax) && tt >= -FLT_MAX && pmax > 0.f) {
+        tt = kPivReg * pmax;
+        ++nreg;
       }
+      const bool ok = tt > 0.f && tt <= FLT_MAX;
+      if (ok) pmax = fmaxf(pmax, tt);
+      fail |= !ok;
+      // pivot sqrt(tt) and its signed inverse from one hardware reciprocal
+      // square root (about 1 ulp)
+      const float rs = ok ? __builtin_amdgcn_rsqf(tt) : 1.f;
+      const float d = ok ? tt * rs : 1.f;
       iv[jj] = sg * rs;
       const float ps = P[jj] * rs;  // L sg below the diagonal
       const float nl = ps * -sg;
       P[jj] = lane == jj ? d : -nl;
-      // the multipliers first, into scalar registers, then the updates: the
-      // broadcasts issue back to back instead of each waiting on the last
-      // one's result
-      float lc[kNB];
 #pragma unroll
-      for (int cc = jj + 1; cc < kNB; ++cc) lc[cc] = readlane(ps, cc);
-#pragma unroll
-      for (int cc = jj + 1; cc < kNB; ++cc) P[cc] = fmaf(lc[cc], nl, P[cc]);
+      for (int cc = jj + 1; cc < kNB; ++cc) P[cc] = fmaf(readlane(ps, cc), nl, P[cc]);
     }
   }
-  return flag;
+  return fail;
+}
+
+// Running maximum over the lanes before this one in its 16-lane row
+// (0 for the first); x >= 0.
+QPD float row_max_before(float x) {
+#define QPK_SHR(v, O) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x110 + O, 0xF, 0xF, true))
+  x = QPK_SHR(x, 1);
+  x = fmaxf(x, QPK_SHR(x, 1));
+  x = fmaxf(x, QPK_SHR(x, 2));
+  x = fmaxf(x, QPK_SHR(x, 4));
+  return fmaxf(x, QPK_SHR(x, 8));
+#undef QPK_SHR
+}
+
+// The same elimination for a panel whose pivots are all good (positive,
+// finite and above kPivTol times the largest before them: the common case).
+// The chain from one pivot to the next bounds the factorisation of every
+// size, so nothing is decided between the columns: the pivots are collected
+// (lane jj holds column jj's) and tested together at the end, with a running
+// maximum across the lanes.  If one needs a decision, the return value is
+// true, pmax and pmaxh are unchanged, and the caller repeats the panel from
+// its saved tiles with eliminate_checked().  Alone on a CU a panel takes 5.7K
+// cycles decided pivot by pivot, 1.7K here.  Rows past the last column
+// (kb < 16) are replaced by rows of the identity first, whose pivots are 1
+// and whose multipliers are 0.
+QPD bool eliminate(float (&P)[kNB], float (&iv)[kNB], int k0, int kb, int npos, float &pmax,
+                   float &pmaxh) {
+  const int lane = tidx() & 63, r = npos - k0;  // columns before r have sign +1
+  if (kb < kNB) {
+#pragma unroll
+    for (int c = 0; c < kNB; ++c)
+      P[c] = lane >= kb ? (lane == c ? (c < r ? 1.f : -1.f) : 0.f) : P[c];
+  }
+  constexpr int kSign = (int)0x80000000;
+  float tv = 0.f;
+  int sm = 0 < r ? 0 : kSign;
+  int tt = __builtin_amdgcn_readlane(__float_as_int(P[0]), 0) ^ sm;
+  float rs = __builtin_amdgcn_rsqf(__int_as_float(tt));
+  // scheduling fences keep the next pivot's chain (update its column, read
+  // the pivot, its reciprocal square root) ahead of this column's other
+  // updates, which then run in the chain's shadow
+#pragma unroll
+  for (int jj = 0; jj < kNB; ++jj) {
+    const float ps = P[jj] * rs;
+    const float nl = __int_as_float(__float_as_int(ps) ^ (sm ^ kSign));
+    float lc[kNB];
+    if (jj + 1 < kNB) P[jj + 1] = fmaf(readlane(ps, jj + 1), nl, P[jj + 1]);
+    const int s0 = sm, t0 = tt;
+    const float rs0 = rs;
+    if (jj + 1 < kNB) {
+      sm = jj + 1 < r ? 0 : kSign;
+      tt = __builtin_amdgcn_readlane(__float_as_int(P[jj + 1]), jj + 1) ^ sm;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int cc = jj + 2; cc < kNB; ++cc) lc[cc] = readlane(ps, cc);
+    if (jj + 1 < kNB) rs = __builtin_amdgcn_rsqf(__int_as_float(tt));
+    __builtin_amdgcn_sched_barrier(0);
+    // (on the diagonal ps sg = tt rs, the pivot's square root)
+    P[jj] = __int_as_float(__float_as_int(ps) ^ s0);
+    iv[jj] = __int_as_float(__float_as_int(rs0) ^ s0);
+    tv = lane == jj ? __int_as_float(t0) : tv;
+#pragma unroll
+    for (int cc = jj + 2; cc < kNB; ++cc) P[cc] = fmaf(lc[cc], nl, P[cc]);
+  }
+  const bool own = lane < kb;
+  tv = own ? tv : 0.f;
+  float before, ph = pmaxh, pm = r == 0 ? 0.f : pmax;
+  if (r == 0) ph = pmax;
+  if (r > 0 && r < kb) {  // the border begins inside the panel
+    const float th = lane < r ? tv : 0.f, tb = lane < r ? 0.f : tv;
+    const float bh = fmaxf(row_max_before(th), pm), bb = row_max_before(tb);
+    before = lane < r ? bh : bb;
+    ph = readlane(fmaxf(bh, th), kNB - 1);
+    pm = readlane(fmaxf(bb, tb), kNB - 1);
+  } else {
+    before = fmaxf(row_max_before(tv), pm);
+    pm = readlane(fmaxf(before, tv), kNB - 1);
+  }
+  if (__any(own && !(tv > kPivTol * before && tv <= FLT_MAX))) return true;
+  pmax = pm;
+  pmaxh = ph;
+  return false;
 }
 
 // The same eliminations on 64 further rows, with the diagonal block D (lanes
@@ -681,14 +777,14 @@ template <int T>
 QPD void border_exponents_done(float el, li *flag) {
   static_assert(T / 64 <= 8, "per-wave exponent slots");
   el = wave_bfly<OpMax>(el);
-  if ((threadIdx.x & 63) == 0) flag[8 + (threadIdx.x >> 6)] = (int)el;
+  if ((tidx() & 63) == 0) flag[8 + (tidx() >> 6)] = (int)el;
 }
 // Wave 0: f(i, k_i) for every border row i with k_i > 0, in row order (a
 // lane per row reads the exponents; the rows to rescale, usually few, are
 // then taken one at a time by the whole wave).
 template <class MF, class F>
 QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
-  const int lane = threadIdx.x & 63, K = N - npos;
+  const int lane = tidx() & 63, K = N - npos;
   for (int k0 = 0; k0 < K; k0 += 64) {
     const int k = k0 + lane;
     const int sh = k < K ? border_shift(M, npos + k, emax) : 0;
@@ -710,9 +806,8 @@ QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
 // panel on the diagonal block and its own rows (eliminate), so that an
 // element of M is read once and written once, and two barriers separate the
 // panels.  A right-looking form reads and writes the trailing matrix once
-// per panel: with the factor in global memory, one tile in flight per wave,
-// that traffic bounded it (64 QPs of n = 256, forward and backward: 56.5 ->
-// 25.6 ms; 1024 of n = 100: 18.5 -> 11.8 ms).
+// per panel: with the factor in global memory that traffic, one tile in
+// flight per wave, took 10 times as long (n = 256).
 // The strict upper part of each row's last 16-column segment is left at
 // exact zeros.  Returns false (uniformly) if a pivot sg_j * a_jj is not a
 // positive finite number.  With dyn, numerically zero pivots are regularised
@@ -723,13 +818,13 @@ QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
 // >= ceil(N / 64).
 template <int T, int RPL, class MF>
 QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *dsh) {
-  M = rflp(M); N = rfl(N); npos = rfl(npos); flag = rflp(flag); dyn = rfl(dyn); dsh = rflp(dsh);
+  M = rflp(M); N = opaque(rfl(N)); npos = opaque(rfl(npos)); flag = rflp(flag); dyn = rfl(dyn); dsh = rflp(dsh);
   constexpr int NW = T / 64;
   constexpr int kMaxBlk = 4 * RPL;            // 16-row blocks of the largest system
   constexpr bool kMore = kMaxBlk > 3 * NW + 1;  // blocks beyond the waves' first slots
   constexpr int DS = 2 * T >= 320 ? 20 : 16;  // row stride of dsh (2 T floats)
   typedef typename Vec4<const MF>::type CV4;
-  const int tid = threadIdx.x, lane = tid & 63, wid = rfl(tid >> 6);
+  const int tid = tidx(), lane = tid & 63, wid = rfl(tid >> 6);
   const int c16 = lane & 15, sl = lane >> 4, g4 = 4 * sl;
   const int nblk = (N + 15) >> 4;
   float pmax = 0.f, pmaxh = 0.f;  // running pivot scale and count of regularised
@@ -738,9 +833,16 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
   // with the pivot tests on, they see the border equilibrated: wave 0
   // scales the rows first and takes the scaling back out of the factor at
   // the end (see border_exponent)
-  const bool eq = dyn && N > npos;
+  bool eq = dyn && N > npos;
   const int emax = eq ? border_emax<T>(flag) : 0;
   if (eq) {
+    // (usually no row needs it; every wave looks)
+    bool any = false;
+    for (int k = lane; k < N - npos; k += 64) any |= border_shift(M, npos + k, emax) > 0;
+    eq = __any(any);
+  }
+  if (eq) {
+    __syncthreads();  // every wave has looked
     if (wid == 0) {
       border_shifted_rows(M, N, npos, emax, [&](int i, int sh) {
         MF *row = M + moff(i);
@@ -793,6 +895,7 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     update_n(used, [&](int u) { return block_of(u + s0); });
     if (wid == 0) *reinterpret_cast<lf4 *>(dsh + c16 * DS + g4) = t[0];
     __syncthreads();
+    QPK_PT(PH_FACT_UPDATE);
     if (used) {
       if (wid != 0) {
         t[3] = t[2]; t[2] = t[1]; t[1] = t[0];
@@ -800,17 +903,10 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
       }
       float P[kNB], iv[kNB];
       tiles_to_rows(t, P);
-      bool again = true;
-      if (kb == kNB) {
-        const float pm = pmax, ph = pmaxh;
-        again = __any(eliminate<false>(P, iv, k0, kNB, npos, dyn, pmax, pmaxh, nreg));
-        if (again) {
-          pmax = pm;
-          pmaxh = ph;
-          tiles_to_rows(t, P);
-        }
+      if (eliminate(P, iv, k0, kb, npos, pmax, pmaxh)) {
+        tiles_to_rows(t, P);
+        fail |= eliminate_checked(P, iv, k0, kb, npos, dyn, pmax, pmaxh, nreg);
       }
-      if (again) fail |= eliminate<true>(P, iv, k0, kb, npos, dyn, pmax, pmaxh, nreg);
       if (wid == 0) {
 #pragma unroll
         for (int c = 1; c < kNB; ++c) P[c] = lane < c ? 0.f : P[c];  // right of the diagonal
@@ -834,6 +930,7 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
       }
     }
     __syncthreads();
+    QPK_PT(PH_FACT_ELIM);
   }
   pmax = fmaxf(pmax, pmaxh);
   if (tid == 0) {
@@ -874,18 +971,6 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
   return good;
 }
 
-// dv[c] = dinv[c] for c < CW (CW a multiple of 4) as 16-byte loads; dinv
-// is allocated in whole 16-entry blocks, and entries past the system's last
-// row are never used.
-template <int CW>
-QPD void load_dinv(const lf *dinv, float (&dv)[CW]) {
-#pragma unroll
-  for (int c = 0; c < CW; c += 4) {
-    const f4v v4 = *reinterpret_cast<const lf4 *>(dinv + c);
-    dv[c] = v4.x; dv[c + 1] = v4.y; dv[c + 2] = v4.z; dv[c + 3] = v4.w;
-  }
-}
-
 // o[t] = p[t] for t < RPL (p aligned to RPL floats) if `in`, else zeros, as
 // one vector load for RPL <= 4 (16-byte loads above).
 template <int RPL, class MF>
@@ -907,108 +992,190 @@ QPD void load_run(const MF *p, bool in, float (&o)[RPL]) {
   }
 }
 
-// Solve (L diag(sg) L') u = r in place for one right-hand side held in
-// `r` (length N), by a single wave with the vector in registers (lane owns
-// rows RPL*lane + t).  The forward sweep walks rows of L, the backward sweep
-// reads L[j][i] from row j; dinv[j] = 1 / L[j][j].  Each 16-column block of L
-// is loaded into registers in bursts of CW columns (all 16, or two halves
-// of 8 when RPL = 16 to bound registers), then its dependent steps run
-// register-only.
-template <int RPL, class MF>
-QPD void signed_solve_wave(const MF *M, int N, int npos, const lf *dinv, lf *r, const MF *zrow) {
+// Solve (L diag(sg) L') u = r in place for the right-hand side r (length N)
+// on WG waves (this one is wave g of them), the vector in registers; dinv[j]
+// = 1 / L[j][j].  The forward sweep walks rows of L, the backward sweep reads
+// L[j][i] from row j.  16-row blocks are dealt to the waves in turn (block b
+// to wave b mod WG), S rows per lane (lane l owns local rows S l .. S l + S-1,
+// all in one block), so that a block's rows sit in fixed slots of 16 / S lanes.
+// For each 16-column block the owner runs its 16 dependent steps (scale the
+// row's value by its dinv, broadcast it, subtract it from every row) in
+// registers; with more than one wave it then passes the 16 values on through
+// `ex` (two buffers of 16, taken in turn, so that one workgroup barrier per
+// block separates writer and readers), and the other waves subtract them from
+// their rows.  Every element sees its subtractions in the same order whatever
+// WG is.  The segments of L do not depend on the chain: the next CW columns'
+// are loaded before this one's steps.  The factor holds exact zeros right of
+// the diagonal inside every row's padded 16-column segment; rows that must
+// not be touched in a block read the zero row `zrow` (16 zeros stored after
+// M's last row, so both pointers are in M's address space), and rows past N-1
+// hold 0 with a dinv of 0, so the steps carry no tests.
+template <int S, int WG, class MF>
+QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r, const MF *zrow,
+                            int g, lf *ex) {
   typedef typename Vec4<const MF>::type CV4;
-  static_assert(kNB % RPL == 0, "row slot must be static within a block");
-  constexpr int CW = RPL > 8 ? 8 : kNB;
-  const int lane = threadIdx.x & 63;
-  // lane l owns rows RPL*l + t, so row j sits in lane j/RPL, slot j%RPL.
-  // The factor holds exact zeros right of the diagonal inside every row's
-  // padded 16-column segment; rows that must not be touched in a block read
-  // the zero row `zrow` (16 zeros stored after M's last row, so both
-  // pointers are in M's address space) instead, so no per-step masking is
-  // needed.  The
-  // diagonal entry is applied by overwriting the owner's value after the FMA.
-  float a[RPL];
+  static_assert(kNB % S == 0, "row slot must be static within a block");
+  // columns in flight: two buffers of S x CW floats per lane
+  constexpr int CW = S > 4 ? 4 : (S > 2 ? 8 : kNB);
+  const int lane = tidx() & 63;
+  const int lr = S * lane;  // this lane's first local row
+  const int i0 = kNB * ((lr >> 4) * WG + g) + (lr & 15);
+  float a[S], dl[S];
+  const MF *row[S];
 #pragma unroll
-  for (int t = 0; t < RPL; ++t) {
-    const int i = RPL * lane + t;
-    a[t] = i < N ? r[i] : 0.f;
+  for (int t = 0; t < S; ++t) {
+    const bool in = i0 + t < N;
+    a[t] = in ? r[min(i0 + t, N - 1)] : 0.f;
+    dl[t] = in ? dinv[min(i0 + t, N - 1)] : 0.f;
+    row[t] = M + moff(min(i0 + t, N - 1));
   }
-  // forward sweep L w = r: w_j = a_j / L[j][j], then a_i -= L[i][j] w_j, i > j
-#pragma unroll 1
-  for (int j0 = 0; j0 < N; j0 += kNB) {
+  const int nblk = (N + 15) >> 4;
+  float nx[S][CW], Lc[S][CW];
+  auto load_f = [&](int j) {  // columns j .. j+CW-1 of this lane's rows
+    const int jb = j & ~15;
 #pragma unroll
-    for (int h = 0; h < kNB; h += CW) {
-      float Lc[RPL][CW], dv[CW];
+    for (int t = 0; t < S; ++t) {
+      // rows below the block: L[i][j..]; rows in the block: their lower part
+      // with zeros right of the diagonal; finished rows and rows past N-1: zeros
+      const MF *p = i0 >= jb && i0 + t < N ? row[t] + j : zrow + (j & 15);
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) {
-        const int i = RPL * lane + t;
-        const bool in = i >= j0 && i < N;
-        // rows below the block: L[i][j0..j0+15]; rows in the block: their
-        // lower part with zeros right of the diagonal; finished rows: zeros
-        const MF *row = in ? M + moff(i) + j0 + h : zrow + h;
-#pragma unroll
-        for (int c = 0; c < CW; c += 4) {
-          const f4v v4 = *reinterpret_cast<CV4 *>(row + c);
-          Lc[t][c] = v4.x; Lc[t][c + 1] = v4.y; Lc[t][c + 2] = v4.z; Lc[t][c + 3] = v4.w;
-        }
+      for (int c = 0; c < CW; c += 4) {
+        const f4v v4 = *reinterpret_cast<CV4 *>(p + c);
+        nx[t][c] = v4.x; nx[t][c + 1] = v4.y; nx[t][c + 2] = v4.z; nx[t][c + 3] = v4.w;
       }
-      load_dinv<CW>(dinv + j0 + h, dv);
+    }
+  };
+  auto take = [&] {
 #pragma unroll
-      for (int c = 0; c < CW; ++c) {
-        const int j = j0 + h + c;
-        if (j < N) {
-          const float wj = readlane(a[(h + c) % RPL], j / RPL) * dv[c];
+    for (int t = 0; t < S; ++t)
 #pragma unroll
-          for (int t = 0; t < RPL; ++t) a[t] = fmaf(-Lc[t][c], wj, a[t]);
-          if (lane == j / RPL) a[(h + c) % RPL] = wj;
+      for (int c = 0; c < CW; ++c) Lc[t][c] = nx[t][c];
+  };
+  // the owner's step for column (or row) c of the block in lanes l0 ..
+  auto step = [&](int h, int c, int l0) {
+    const int q = h + c, s = q % S;
+    const float w = a[s] * dl[s];
+    const float wj = readlane(w, l0 + q / S);
+#pragma unroll
+    for (int t = 0; t < S; ++t) a[t] = fmaf(-Lc[t][c], wj, a[t]);
+    a[s] = lane == l0 + q / S ? w : a[s];
+  };
+  // pass the block's values on (their owner) or subtract them (the others)
+  auto give = [&](int l0, lf *e) {
+    if (lane >= l0 && lane < l0 + kNB / S) {
+#pragma unroll
+      for (int t = 0; t < S; ++t) e[S * (lane - l0) + t] = a[t];
+    }
+  };
+  load_f(0);
+#pragma unroll 1
+  for (int b = 0; b < nblk; ++b) {
+    const int l0 = (kNB / S) * (b / WG);
+    const bool own = WG == 1 || b % WG == g;
+    lf *e = ex + 16 * (b & 1);
+    if (own) {
+#pragma unroll
+      for (int h = 0; h < kNB; h += CW) {
+        take();
+        load_f(min(kNB * b + h + CW, kNB * nblk - CW));
+#pragma unroll
+        for (int c = 0; c < CW; ++c) step(h, c, l0);
+      }
+      if constexpr (WG > 1) give(l0, e);
+    }
+    if constexpr (WG > 1) {
+      __syncthreads();
+      if (!own) {
+#pragma unroll
+        for (int h = 0; h < kNB; h += CW) {
+          take();
+          load_f(min(kNB * b + h + CW, kNB * nblk - CW));
+#pragma unroll
+          for (int c = 0; c < CW; c += 4) {
+            const f4v w4 = *reinterpret_cast<const lf4 *>(e + h + c);
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+              for (int t = 0; t < S; ++t) a[t] = fmaf(-Lc[t][c + cc], w4[cc], a[t]);
+          }
         }
       }
     }
   }
   // sign: w <- sg w
 #pragma unroll
-  for (int t = 0; t < RPL; ++t) {
-    const int i = RPL * lane + t;
-    if (i >= npos) a[t] = -a[t];
-  }
+  for (int t = 0; t < S; ++t)
+    if (i0 + t >= npos) a[t] = -a[t];
   // backward sweep L' u = w: u_j = a_j / L[j][j], then a_i -= L[j][i] u_j, i < j
+  auto load_b = [&](int j) {  // rows j .. j+CW-1 at this lane's columns
+    // rows b0 .. b0+15 are one block: row b0+c starts c * rstride floats
+    // after row b0 (the last rows, past N-1, read row N-1)
+    const int b0 = j & ~15, h = j & 15, rstride = 20 + b0;
+    const MF *brow = M + moff(b0) + i0;
+    // rows above the block read row j; rows in the block read row j's
+    // zero padding right of its diagonal; rows below read zeros.  A lane's
+    // S rows are all above the block or all at or below it.
+    const bool above = i0 < b0 + kNB;
+#pragma unroll
+    for (int c = 0; c < CW; ++c) {
+      float run[S];
+      load_run<S>(brow + min(h + c, N - 1 - b0) * rstride, above, run);
+#pragma unroll
+      for (int t = 0; t < S; ++t) nx[t][c] = run[t];
+    }
+  };
+  load_b(kNB * nblk - CW);
 #pragma unroll 1
-  for (int b0 = ((N - 1) / kNB) * kNB; b0 >= 0; b0 -= kNB) {
+  for (int b = nblk - 1; b >= 0; --b) {
+    const int l0 = (kNB / S) * (b / WG);
+    const bool own = WG == 1 || b % WG == g;
+    lf *e = ex + 16 * (b & 1);
+    if (own) {
 #pragma unroll
-    for (int h = kNB - CW; h >= 0; h -= CW) {
-      float Lr[RPL][CW], dv[CW];
-      // rows b0 .. b0+15 are one block: row b0+c starts c * rstride floats
-      // after row b0 (the last rows, past N-1, read row N-1)
-      const int rstride = 20 + 16 * (b0 >> 4);
-      const MF *brow = M + moff(b0) + RPL * lane;
-      // rows above the block read row j; rows in the block read row j's
-      // zero padding right of its diagonal; rows below read zeros.  A lane's
-      // RPL rows are all above the block or all at or below it.
-      const bool above = RPL * lane < b0 + kNB;
+      for (int h = kNB - CW; h >= 0; h -= CW) {
+        take();
+        load_b(max(kNB * b + h - CW, 0));
 #pragma unroll
-      for (int c = 0; c < CW; ++c) {
-        float run[RPL];
-        load_run<RPL>(brow + min(h + c, N - 1 - b0) * rstride, above, run);
-#pragma unroll
-        for (int t = 0; t < RPL; ++t) Lr[t][c] = run[t];
+        for (int c = CW - 1; c >= 0; --c) step(h, c, l0);
       }
-      load_dinv<CW>(dinv + b0 + h, dv);
+      if constexpr (WG > 1) give(l0, e);
+    }
+    if constexpr (WG > 1) {
+      __syncthreads();
+      if (!own) {
 #pragma unroll
-      for (int c = CW - 1; c >= 0; --c) {
-        const int j = b0 + h + c;
-        if (j < N) {
-          const float uj = readlane(a[(h + c) % RPL], j / RPL) * dv[c];
+        for (int h = kNB - CW; h >= 0; h -= CW) {
+          take();
+          load_b(max(kNB * b + h - CW, 0));
 #pragma unroll
-          for (int t = 0; t < RPL; ++t) a[t] = fmaf(-Lr[t][c], uj, a[t]);
-          if (lane == j / RPL) a[(h + c) % RPL] = uj;
+          for (int c = CW - 4; c >= 0; c -= 4) {
+            const f4v w4 = *reinterpret_cast<const lf4 *>(e + h + c);
+#pragma unroll
+            for (int cc = 3; cc >= 0; --cc)
+#pragma unroll
+              for (int t = 0; t < S; ++t) a[t] = fmaf(-Lc[t][c + cc], w4[cc], a[t]);
+          }
         }
       }
     }
   }
 #pragma unroll
-  for (int t = 0; t < RPL; ++t) {
-    const int i = RPL * lane + t;
-    if (i < N) r[i] = a[t];
+  for (int t = 0; t < S; ++t)
+    if (i0 + t < N) r[i0 + t] = a[t];
+}
+
+// The solves of one or two right-hand sides side by side: up to 4 rows per
+// lane one wave each (the chain of dependent steps bounds them), above that
+// half of the workgroup's waves each.  A barrier must follow.
+template <int T, int RPL, class MF>
+QPD void signed_solve(const MF *M, int N, int npos, const lf *dinv, lf *r0, lf *r1, bool both,
+                      const MF *zrow, lf *ex) {
+  constexpr int WG = RPL > 4 ? T / 128 : 1, S = RPL / WG;
+  const int wid = rfl(tidx() >> 6), k = wid / WG;
+  if (k == 0 || (k == 1 && both)) {
+    signed_solve_waves<S, WG>(M, N, npos, dinv, k ? r1 : r0, zrow, wid % WG, ex + 32 * k);
+  } else if constexpr (WG > 1) {
+    for (int b = 2 * ((N + 15) >> 4); b > 0; --b) __syncthreads();
   }
 }
 
@@ -1020,7 +1187,7 @@ QPD float coldot_d(const RF *R, int ld, int rows, int cols, const XF *x,
   float mx = 0.f;  // largest |column sum| this thread produced
   const int cw = cols <= 64 ? 64 : (cols <= 128 ? (T >= 128 ? 128 : 64) : (T >= 256 ? 256 : T));
   const int groups = T / cw;
-  const int g = threadIdx.x / cw, jl = threadIdx.x % cw;
+  const int g = tidx() / cw, jl = tidx() % cw;
   for (int jb = 0; jb < cols; jb += cw) {
     const int j = jb + jl;
     AT acc = 0;
@@ -1029,7 +1196,7 @@ QPD float coldot_d(const RF *R, int ld, int rows, int cols, const XF *x,
 #pragma unroll 8
       for (int i = g; i < rows; i += groups) acc = fma((AT)R[(size_t)i * ld + j], (AT)x[i], acc);
     }
-    part[threadIdx.x] = acc;
+    part[tidx()] = acc;
     __syncthreads();
     if (g == 0 && j < cols) {
       AT s = 0;
@@ -1061,7 +1228,7 @@ QPD void kkt_matvecs(const gf *Q, const gf *G, const gf *A, int n, int m, int p,
                      typename LdsT<AT>::type *part, float &mq, float &mg, float &ma) {
   typedef typename LdsT<AT>::type la;
   constexpr int RG = T / 16;
-  const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4, wid = tid >> 6;
+  const int tid = tidx(), sub = tid & 15, grp = tid >> 4, wid = tid >> 6;
   mq = mg = ma = 0.f;
   for (int jb = 0; jb < n; jb += 64) {
     AT xv[4], cq[4], cg[4], ca[4];
@@ -1147,7 +1314,7 @@ enum CtxSlot {
   CS_GH = 54, CS_N = 56
 };
 static __shared__ unsigned qpk_ctab[CS_N];
-static_assert(CS_N * 4 + 16 * 8 <= kStaticLds, "static LDS bound of the launch planning");
+static_assert(CS_N * 4 <= kStaticLds, "static LDS bound of the launch planning");
 
 // A context address: reads entry K of the table (PT carries the address
 // space, 32-bit LDS or 64-bit global addresses).
@@ -1202,7 +1369,6 @@ struct Ctx {
   int rmode;  // residual precision: 0 FP32 first (FP64 refinement after a
               // stall), 1 FP64 residuals everywhere, 2 FP32 only
   float bo;   // line-search back-off factor (1 = none)
-  __attribute__((address_space(3))) long long *pt;
 };
 
 // Sizes and scalar settings of the context, and (thread 0) the address
@@ -1211,7 +1377,7 @@ template <class MF>
 QPD void init_ctx(Ctx<MF> &C, lf *sm, const Layout &L, MF *Mptr, const gf *Qg, const gf *qg,
                   const gf *Ag, const gf *bg, const gf *Gg, const gf *hg) {
   C.n = L.n; C.m = L.m; C.p = L.p; C.kb = L.kb;
-  if (threadIdx.x == 0) {
+  if (tidx() == 0) {
     C.Q.set(Qg); C.q_g.set(qg); C.A.set(Ag); C.b_g.set(bg); C.G.set(Gg); C.h_g.set(hg);
     C.M.set(Mptr);
     C.x.set(sm + L.x); C.y.set(sm + L.y); C.z.set(sm + L.z); C.s.set(sm + L.s);
@@ -1236,7 +1402,6 @@ QPD void init_ctx(Ctx<MF> &C, lf *sm, const Layout &L, MF *Mptr, const gf *Qg, c
   C.dyn = 1;
   C.rmode = 0;
   C.bo = 1.f;
-  C.pt = nullptr;  // set by profiling builds
 }
 
 
@@ -1245,9 +1410,8 @@ QPD void init_ctx(Ctx<MF> &C, lf *sm, const Layout &L, MF *Mptr, const gf *Qg, c
 template <class MF>
 QPD Ctx<MF> uctx(const Ctx<MF> &I) {
   Ctx<MF> C;
-  C.n = rfl(I.n); C.m = rfl(I.m); C.p = rfl(I.p); C.kb = rfl(I.kb);
+  C.n = opaque(rfl(I.n)); C.m = opaque(rfl(I.m)); C.p = opaque(rfl(I.p)); C.kb = opaque(rfl(I.kb));
   C.amode = rfl(I.amode); C.dyn = rfl(I.dyn); C.rmode = rfl(I.rmode); C.bo = rflf(I.bo);
-  C.pt = rflp(I.pt);
   return C;
 }
 
@@ -1265,7 +1429,7 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
   CT C = uctx(Cin_);
   bounded = rfl(bounded); kappa = rflf(kappa); kr = rflf(kr);
   typedef typename LdsT<AT>::type la;
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   // one accumulator for Qx + G'z + A'y; the pieces' norms are taken as they
   // are produced
   la *gxd = reinterpret_cast<la *>(C.dd.get()), *axd = gxd + m, *rtd = gxd + m + p;
@@ -1276,6 +1440,7 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
   for (int k = 0; k < NK; ++k) mx[k] = 0.f;
   kkt_matvecs<T, AT>(C.Q, C.G, C.A, n, m, p, C.x, C.z, true, C.y, gxd, axd, rtd, pd, mx[QX],
                      mx[GZ], mx[AY]);
+  QPK_PT(PH_MATVEC);
   const bool man = bounded && kr > 0.f;  // relaxation of an implicit form
   for (int i = tid; i < n; i += T) {
     const float r = (float)(rtd[i] + (AT)C.q[i]);
@@ -1330,7 +1495,7 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
 // Writes the compacted indices to out[] and returns the count (uniform).
 template <int T>
 QPD int compact_rows(const li *flag, int m, li *out, lf *red) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = tidx(), lane = tid & 63, w = tid >> 6;
   int base = 0;
   for (int i0 = 0; i0 < m; i0 += T) {
     const int i = i0 + tid;
@@ -1362,7 +1527,7 @@ template <int T, class CT>
 QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
   CT C = uctx(Cin_);
   kappa = rflf(kappa);
-  const int m = C.m, kb = C.kb, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int m = C.m, kb = C.kb, tid = tidx(), lane = tid & 63, w = tid >> 6;
   constexpr int NW = T / 64;
   li *ws = reinterpret_cast<li *>(C.red.get());  // per-wave counts [2][NW]
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -1489,7 +1654,7 @@ __host__ __device__ inline int stage_floats(int n) { return ((n + 15) & ~15) * k
 template <int T, class CT>
 QPD void assemble_h_mfma(CT &C, int ne, const lf *wts) {
   constexpr int W = T / 64;
-  const int n = C.n, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int n = C.n, tid = tidx(), lane = tid & 63, wid = tid >> 6;
   const int n16 = (n + 15) & ~15, nt = n16 >> 4;
   const int ntl = nt * (nt + 1) / 2;
   const int passes = (ntl + W * kAsmTiles - 1) / (W * kAsmTiles);
@@ -1590,7 +1755,7 @@ template <int T, class CT>
 QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, float delta) {
   CT C = uctx(Cin_);
   nb = rfl(nb); ne = rfl(ne); wts = rflp(wts); bounded = rfl(bounded); delta = rflf(delta);
-  const int n = C.n, p = C.p, tid = threadIdx.x;
+  const int n = C.n, p = C.p, tid = tidx();
   auto *M = C.M.get();
   if (C.amode != 0) {
     assemble_h_mfma<T>(C, ne, wts);
@@ -1698,6 +1863,7 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
   }
   }
   __syncthreads();
+  QPK_PT(PH_ASM);
   // border rows: [C | -Dl (lower part)].  C = [G_B; A] copied by 16 lanes
   // per row, which also take each row's squared norm for the border
   // equilibration of the factorisation (border_exponent); then the lower
@@ -1723,6 +1889,7 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
     }
     border_exponents_done<T>(el, C.iflag);
   }
+  QPK_PT(PH_ASM_BORDER);
   for (int e = tid; e < K * K; e += T) {
     const int k = e / K, l = e - k * K;
     if (l > k) continue;
@@ -1743,24 +1910,16 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
 // dinv[j] = 1 / L[j][j]
 template <int T, class CT>
 QPD void make_dinv(CT &C, int N) {
-  for (int j = threadIdx.x; j < N; j += T) C.dinv[j] = 1.f / C.M[moff(j) + j];
+  for (int j = tidx(); j < N; j += T) C.dinv[j] = 1.f / C.M[moff(j) + j];
   __syncthreads();
 }
 
-// Solve for both right-hand sides u0 and u1 (wave 0 and wave 1 in parallel
-// when the workgroup has two waves).
+// Solve for u0 or both right-hand sides u0 and u1.
 template <int T, int RPL, class CT>
 QPK_PHASE void solve2(CT &Cin_, int N, bool both) {
   CT C = uctx(Cin_);
   N = rfl(N); both = rfl(both);
-  const int wid = threadIdx.x >> 6;
-  if constexpr (T >= 128) {
-    if (wid == 0) signed_solve_wave<RPL>(C.M.get(), N, C.n, C.dinv, C.u0, C.mz.get());
-    else if (wid == 1 && both) signed_solve_wave<RPL>(C.M.get(), N, C.n, C.dinv, C.u1, C.mz.get());
-  } else {
-    signed_solve_wave<RPL>(C.M.get(), N, C.n, C.dinv, C.u0, C.mz.get());
-    if (both) signed_solve_wave<RPL>(C.M.get(), N, C.n, C.dinv, C.u1, C.mz.get());
-  }
+  signed_solve<T, RPL>(C.M.get(), N, C.n, C.dinv, C.u0, C.u1, both, C.mz.get(), C.part);
   __syncthreads();
 }
 
@@ -1787,7 +1946,7 @@ constexpr float kRefineSlow = 0.5f;
 template <int T, class AT, class CT>
 QPD void kkt_apply(CT &C, int nb, bool bounded, const lf *w, const lf *u, lf *out, bool sub) {
   typedef typename LdsT<AT>::type la;
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   la *gx = reinterpret_cast<la *>(C.dd.get()), *ax = gx + m, *phi = gx + m + p, *kx = gx + 2 * m + p;
   la *pd = reinterpret_cast<la *>(C.part.get());
   // G u, A u and Q'u_x + A'u_y in one pass; then G' phi, which needs G u
@@ -1817,7 +1976,7 @@ QPD void kkt_apply(CT &C, int nb, bool bounded, const lf *w, const lf *u, lf *ou
 template <int T>
 QPD float maxnorm(const lf *r, int N, lf *red) {
   float mx[2] = {0.f, 0.f};
-  for (int j = threadIdx.x; j < N; j += T) {
+  for (int j = tidx(); j < N; j += T) {
     const float a = fabsf(r[j]);
     mx[0] = fmaxf(mx[0], a);
     if (!(a <= FLT_MAX)) mx[1] = 1.f;
@@ -1845,11 +2004,12 @@ template <int T, int RPL, class AT, class CT>
 QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int steps) {
   CT C = uctx(Cin_);
   nb = rfl(nb); bounded = rfl(bounded); w = rflp(w); u = rflp(u); steps = rfl(steps);
-  const int n = C.n, p = C.p, tid = threadIdx.x, N = n + nb + p;
+  const int n = C.n, p = C.p, tid = tidx(), N = n + nb + p;
   lf *r = C.rr;
   float prev = 0.f, first = 0.f, cur = 0.f;
   for (int it = 0; it <= steps; ++it) {
     kkt_apply<T, AT>(C, nb, bounded, w, u, r, true);
+    QPK_PT(PH_REFINE_APPLY);
     const float nrm = maxnorm<T>(r, N, C.red);
     cur = nrm;
     if (it > 0) {
@@ -1866,7 +2026,7 @@ QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int s
     }
     if (it == steps) break;
     prev = nrm;
-    if (threadIdx.x < 64) signed_solve_wave<RPL>(C.M.get(), N, n, C.dinv, r, C.mz.get());
+    signed_solve<T, RPL>(C.M.get(), N, n, C.dinv, r, r, false, C.mz.get(), C.part);
     __syncthreads();
     for (int j = tid; j < N; j += T) {
       C.rd[j] = r[j];
@@ -1874,7 +2034,7 @@ QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int s
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) C.iflag[7] = __float_as_int(cur);
+  if (tidx() == 0) C.iflag[7] = __float_as_int(cur);
   __syncthreads();
   return first;
 }
@@ -1893,7 +2053,7 @@ QPD float refine_policy(CT &C, int nb, bool bounded, const lf *w, lf *u, int ste
     q = refine<T, RPL, float>(C, nb, bounded, w, u, steps);
     if (C.rmode == 0 && !(q <= kRefineSlow)) {
       __syncthreads();
-      if (threadIdx.x == 0) C.iflag[5] = 1;
+      if (tidx() == 0) C.iflag[5] = 1;
       __syncthreads();
       q = refine<T, RPL, double>(C, nb, bounded, w, u, steps);
     }
@@ -1919,7 +2079,7 @@ template <int T, class CT>
 QPK_PHASE void border_delta(CT &Cin_, int nb, float rel, float floor_abs) {
   CT C = uctx(Cin_);
   nb = rfl(nb); rel = rflf(rel); floor_abs = rflf(floor_abs);
-  const int n = C.n, K = nb + C.p, tid = threadIdx.x;
+  const int n = C.n, K = nb + C.p, tid = tidx();
   float mx[2] = {0.f, 0.f};
   for (int j = tid; j < n; j += T) mx[0] = fmaxf(mx[0], C.M[moff(j) + j]);
   for (int k = tid; k < K; k += T) {
@@ -1941,7 +2101,7 @@ QPK_PHASE void border_delta(CT &Cin_, int nb, float rel, float floor_abs) {
 template <int T>
 QPD bool any_nonfinite(const lf *a, const lf *b, bool two, int N, lf *red) {
   float f[1] = {0.f};
-  for (int j = threadIdx.x; j < N; j += T) {
+  for (int j = tidx(); j < N; j += T) {
     if (!finitef(a[j]) || (two && !finitef(b[j]))) f[0] = 1.f;
   }
   block_reduce<T, OpMax, 1>(f, red);
@@ -1964,9 +2124,9 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
   } else if (delta_rel > 0.f) {
     border_delta<T>(C, nb, delta_rel, 0.f);
   }
-  QPK_PT(C, PH_ASM);
+  QPK_PT(PH_ASM_DIAG);
   bool ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, C.dyn != 0, C.part);
-  QPK_PT(C, PH_FACT);
+  QPK_PT(PH_FACT);
   *regularised = delta_rel > 0.f || floor || C.iflag[2] > 0;
   if (!ok && C.dyn) {
     // the floor is at least kRetryReg times the largest pivot the failed
@@ -1993,7 +2153,7 @@ QPK_PHASE void rhs_bounded(CT &Cin_, int nb, float kappa, const gf *gx, const gf
   CT C = uctx(Cin_);
   nb = rfl(nb); kappa = rflf(kappa); adj = rfl(adj);
   gx = rflp(gx); gz = rflp(gz); gy = rflp(gy);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   // phi0 = -(r_i + r_z - r_s) + psi0 would give u_x = -r_t - G' phi0;
   // we compute w0 = (r_i + r_z - r_s) - psi0 so u_x = -r_t + G' w0, and
   // w1 = -psi1 so u_x1 = G' w1.
@@ -2056,7 +2216,7 @@ template <int T, class CT>
 QPK_PHASE void recover_bounded(CT &Cin_, int nb, bool both) {
   CT C = uctx(Cin_);
   nb = rfl(nb); both = rfl(both);
-  const int n = C.n, m = C.m, tid = threadIdx.x;
+  const int n = C.n, m = C.m, tid = tidx();
   if (!m) return;
   if (both) {
     const lf *xv[2] = {C.u0, C.u1};
@@ -2108,7 +2268,7 @@ template <int T, int RPL, class CT>
 QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
   CT C = uctx(Cin_);
   dyn = rfl(dyn);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   for (int i = tid; i < m; i += T) C.E[i] = 1.f;  // unit weights
   for (int i = tid; i < m; i += T) C.role[i] = 1;
   __syncthreads();
@@ -2169,11 +2329,11 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
   CT C = uctx(Cin_);
   kappa = rflf(kappa); kt_mode = rfl(kt_mode); sigma = rflf(sigma); kr = rflf(kr);
   delta_reg = rflf(delta_reg); refine_steps = rfl(refine_steps);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   C.amode = rfl(C.iflag[3]);  // this QP's assembly arithmetic (may have fallen back)
   const int nb = partition_bounded<T>(C, kappa);
   const int ne = C.iflag[1];
-  QPK_PT(C, PH_PART);
+  QPK_PT(PH_PART);
   const int N = n + nb + p;
   const double dn = n, dm = m, dp = p, dN = N;
   work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;            // residuals
@@ -2193,8 +2353,9 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     work += 2.0 * (2.0 * dN * dN + 4.0 * dm * dn);                  // two solves
     if (!ok) break;
     make_dinv<T>(C, N);
+    QPK_PT(PH_DINV);
     rhs_bounded<T>(C, nb, kappa, nullptr, nullptr, nullptr, false);
-    QPK_PT(C, PH_RHS);
+    QPK_PT(PH_RHS);
     const int nref = (reg || C.amode == 1) ? max(refine_steps, 2)
                                            : plain_refine_steps(C.rmode, refine_steps, 0);
     if (nref) {
@@ -2202,7 +2363,7 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
       __syncthreads();
     }
     solve2<T, RPL>(C, N, true);
-    QPK_PT(C, PH_SOLVE);
+    QPK_PT(PH_SOLVE);
     if (nref) {
       const float q0 = refine_policy<T, RPL>(C, nb, true, C.w0, C.u0, nref);
       const float q1 = refine_policy<T, RPL>(C, nb, true, C.w1, C.u1, nref);
@@ -2223,9 +2384,9 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     break;
   }
   if (!ok) { *stage = SG_PRED; return ST_FACT; }
-  QPK_PT(C, PH_REFINE);
+  QPK_PT(PH_REFINE);
   recover_bounded<T>(C, nb, true);
-  QPK_PT(C, PH_RECOVER);
+  QPK_PT(PH_RECOVER);
   // predictor step length (kappa_target = 0) and kappa_aff
   float kt;
   if (kt_mode == 0) {
@@ -2254,6 +2415,7 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     kt = sg * kappa;
     if (!finitef(kt)) { *stage = SG_CENT; return ST_NONFIN; }
     kt = fmaxf(kt, 1e-12f);  // keep the central-path parameter positive
+    QPK_PT(PH_AFFINE);
   } else if (kt_mode == 1) {
     kt = sigma * kappa;
   } else {
@@ -2289,7 +2451,7 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
   }
   kappa = knew;
   __syncthreads();
-  QPK_PT(C, PH_STEP);
+  QPK_PT(PH_STEP);
   return ST_CONV;
 }
 
@@ -2299,7 +2461,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
                         int *stage) {
   CT C = uctx(Cin_);
   mu = rflf(mu); kt_mode = rfl(kt_mode); kr = rflf(kr); delta_reg = rflf(delta_reg);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   float bad[1] = {0.f};
   for (int i = tid; i < m; i += T) {
     const float w = C.z[i] / C.s[i];
@@ -2411,7 +2573,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
 // vector attains.  Uses r_t, r_e from residuals(); uniform result.
 template <int T, class CT>
 QPD float direct_backward_error(CT &C) {
-  const int n = C.n, p = C.p, tid = threadIdx.x;
+  const int n = C.n, p = C.p, tid = tidx();
   float mx[4] = {0.f, 0.f, 0.f, 0.f};  // |r_t|, its scale, |r_e|, its scale
   for (int j = tid; j < n; j += T) {
     float a = fabsf(C.q[j]);
@@ -2436,7 +2598,7 @@ template <int T, int RPL, class CT>
 QPD int newton_loop(CT &C, bool bounded, int max_iter, float tol, int kt_mode, float sigma,
                     float kr, float delta_reg, int refine_steps, double &work, int &iters,
                     float &res) {
-  const int m = C.m, tid = threadIdx.x;
+  const int m = C.m, tid = tidx();
   int status = ST_MAXIT;
   int stage = SG_NONE;
   for (int it = 0;; ++it) {
@@ -2448,13 +2610,14 @@ QPD int newton_loop(CT &C, bool bounded, int max_iter, float tol, int kt_mode, f
     }
     block_reduce<T, OpSum, 1>(sm, C.red);
     float kappa = m ? sm[0] / (float)m : 0.f;
+    QPK_PT(PH_KAPPA);
     bool bad = false;
     // FP64 residuals under the FP64 policy, and for a QP whose refinement
     // has already needed FP64 (FP32 cannot resolve its residuals either)
     const bool r64 = C.rmode == 1 || (C.rmode == 0 && C.iflag[5] != 0);
     res = r64 ? residuals<T, double>(C, bounded, kappa, kt_mode == 2 ? kr : 0.f, &bad)
               : residuals<T, float>(C, bounded, kappa, kt_mode == 2 ? kr : 0.f, &bad);
-    QPK_PT(C, PH_RESID);
+    QPK_PT(PH_RESID);
     if (bad || !finitef(res)) {
       status = ST_NONFIN;
       stage = kt_mode == 2 ? SG_RELAX : (it == 0 ? SG_NONE : SG_LS);
@@ -2494,7 +2657,7 @@ QPD int newton_loop(CT &C, bool bounded, int max_iter, float tol, int kt_mode, f
 // Load this QP's small vectors into LDS.
 template <int T, class CT>
 QPD void load_vectors(CT &C) {
-  const int tid = threadIdx.x;
+  const int tid = tidx();
   for (int i = tid; i < C.n; i += T) C.q[i] = C.q_g[i];
   for (int i = tid; i < C.m; i += T) C.h[i] = C.h_g[i];
   for (int i = tid; i < C.p; i += T) C.b[i] = C.b_g[i];
@@ -2517,7 +2680,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
   CT C = uctx(Cin_);
   bounded = rfl(bounded); gx = rflp(gx); gy = rflp(gy); gz = rflp(gz);
   delta_reg = rflf(delta_reg); refine_steps = rfl(refine_steps);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   float sm[1] = {0.f};
   for (int i = tid; i < m; i += T) {
     sm[0] += C.s[i] * C.z[i];
@@ -2651,7 +2814,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
 template <int T, class CT>
 QPK_PHASE void write_grads(CT &Cin_, const Params &P, size_t qi) {
   CT C = uctx(Cin_);
-  const int n = C.n, m = C.m, p = C.p, tid = threadIdx.x;
+  const int n = C.n, m = C.m, p = C.p, tid = tidx();
   const lf *dx = C.u0, *dy = C.u0 + n, *dz = C.dv0;
   if (P.dQ) {
     gf *o = (gf *)P.dQ + qi * (size_t)n * n;
@@ -2727,7 +2890,7 @@ QPD void qp_body(const Params &P) {
   else C.amode = P.asm_mode;
   const int amode0 = C.amode;
   const int refine = P.refine;
-  const int tid = threadIdx.x;
+  const int tid = tidx();
   // per-QP assembly mode for the Newton steps (a BF16x3 QP may fall back)
   if (tid == 0) C.iflag[3] = C.amode;
   // implicit complementarity (bounded form 0, or the first partially
@@ -2741,11 +2904,9 @@ QPD void qp_body(const Params &P) {
     C.iflag[5] = 0;  // refinement residuals start in FP32
   }
 #ifdef QPK_PHASE_TIMING
-  __shared__ long long pt_acc[PH_N];
-  C.pt = (__attribute__((address_space(3))) long long *)pt_acc;
-  if (tid < PH_N) C.pt[tid] = 0;
+  if (tid < PH_N) qpk_pt[tid] = 0;
   __syncthreads();
-  if (tid == 0) C.pt[15] = clock64();
+  if (tid == 0) qpk_pt[PH_N - 1] = clock64();
 #endif
   load_vectors<T>(C);
   double work = 0.0;
@@ -2806,7 +2967,7 @@ QPD void qp_body(const Params &P) {
     }
   } else if constexpr (MODE == kSolve) {
     const bool ok = initialize<T, RPL>(C, work, C.dyn != 0);
-    QPK_PT(C, PH_INIT);
+    QPK_PT(PH_INIT);
     if (!ok) {
       status = mkstatus(ST_FACT, SG_PRED);
       res = __int_as_float(0x7fc00000);
@@ -2856,7 +3017,7 @@ QPD void qp_body(const Params &P) {
     const gf *gy = P.gy ? (const gf *)P.gy + qi * (size_t)p : nullptr;
     const gf *gz = P.gz ? (const gf *)P.gz + qi * (size_t)m : nullptr;
     const int adj = adjoint<T, RPL>(C, bounded, gx, gy, gz, P.delta_reg, refine, work);
-    QPK_PT(C, PH_BWD);
+    QPK_PT(PH_BWD);
     // Algorithm 2 hands the factorisation at the relaxed point to the
     // gradient computation, so a breakdown there counts as a relax failure;
     // an adjoint solve whose refinement stalled is reported at the backward
@@ -2878,8 +3039,8 @@ QPD void qp_body(const Params &P) {
     }
   }
 #ifdef QPK_PHASE_TIMING
-  QPK_PT(C, PH_OUT);
-  if (P.phase && tid < PH_N - 1) P.phase[qi * PH_N + tid] = C.pt[tid];
+  QPK_PT(PH_OUT);
+  if (P.phase && tid < PH_N - 1) P.phase[qi * PH_N + tid] = qpk_pt[tid];
 #endif
 }
 
