@@ -284,31 +284,61 @@ __host__ __device__ inline int moff(int i) {
   return 20 * i + 16 * (8 * q * (q - 1) + q * rem);
 }
 
-// Lower-triangular tile t -> (ti, tj), tj <= ti, in row order.
+// Addresses inside a factor of N rows.  In LDS the packed-blocked layout
+// above.  In global memory 16x16 tiles, row-major and contiguous, tile row by
+// tile row (the last one only as many rows as the system has), so that a wave
+// reads or writes a tile as one run of 1 KB: with rows kept contiguous instead,
+// a tile is 16 runs of 64 bytes in as many pairs of cache lines, and a read
+// with a row per lane is 64 of them.  Either takes at most moff(N) floats.
+// Row i: element (i, j) is at base + col(j); block q of 16 rows: the segment
+// of panel k of its row r is at row(16 q + r).base + k step.
+template <class MF>
+struct MRow {
+  int base, step;
+  QPD int col(int j) const {
+    if constexpr (std::is_same<MF, lf>::value) return j;
+    else return (j >> 4) * step + (j & 15);
+  }
+  QPD int at(int j) const { return base + col(j); }
+};
+template <class MF>
+QPD MRow<MF> mrow(int N, int i) {
+  if constexpr (std::is_same<MF, lf>::value) {
+    return {moff(i), kNB};
+  } else {
+    const int q = i >> 4, last = (N - 1) >> 4;
+    return {128 * q * (q + 1) + 16 * (i & 15), q == last ? 16 * (N - 16 * last) : 256};
+  }
+}
+
+// Lower-triangular tile t -> (ti, tj), tj <= ti, in row order.  The estimate
+// is off by at most one for the tile counts in use (below 2^15).
 QPD void tile_ij(int t, int &ti, int &tj) {
-  int i = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-  while ((i + 1) * (i + 2) / 2 <= t) ++i;
-  while (i * (i + 1) / 2 > t) --i;
+  int i = (int)((__builtin_amdgcn_sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+  i += (i + 1) * (i + 2) / 2 <= t;
+  i -= i * (i + 1) / 2 > t;
   ti = i;
   tj = t - i * (i + 1) / 2;
 }
 
 // ---------------------------------------------------------------------------
 // Per-QP LDS layout (floats; ints share the float arena).  All blocks are
-// 4-float aligned.
+// 4-float aligned.  Equal sizes stand together, so that an address is a few
+// scalar multiply-adds of the sizes away: every phase works its addresses out
+// anew (Ctx) instead of keeping them.
 struct Layout {
-  int n, m, p, kb, Nmax, ld;
-  int x, y, z, s, v, q, h, b;
-  int E, D, c;
-  int rt, ri, re, rz, rs;
-  int tGz, tAy;
-  int t0, t1, u0, u1, dv0, dv1, dinv;
-  int part, red;
-  int w0, w1, rr, rd, dd;  // rhs copies / residual and last correction of
-                           // the refinement; FP64 scratch
-  int pan;             // (unused)
-  int role, bidx, elist, iflag;
-  int stg, stg_len;  // assembly staging: the span u0 .. end of dd, which
+  int n, m, p, kb, Nmax;
+  int iflag;                            // 16 flags
+  int part, red;                        // partial sums, reduction scratch
+  int u0, u1, rr, rd;                   // right-hand sides; residual and last
+                                        // correction of the refinement
+  int dv0, dv1, dd, dinv;               // dd: FP64 scratch
+  int z, s, v, h, E, D, c, ri, rz, rs;
+  int role, bidx, elist;
+  int t0, t1;                           // also rhs copies of the refinement
+  int x, q, rt, tGz, tAy;
+  int y, b, re;
+  int stg, stg_len;  // assembly staging: the span part .. end of dinv, which
                      // holds nothing live while the matrix is assembled
   int M;      // offset of M if in LDS, else -1
   int total;  // floats
@@ -316,63 +346,68 @@ struct Layout {
 
 __host__ __device__ inline int al4(int a) { return (a + 3) & ~3; }
 
-
 __host__ __device__ inline Layout make_layout(int n, int m, int p, int kb, bool m_lds, int T) {
   Layout L;
   L.n = n; L.m = m; L.p = p; L.kb = kb;
   L.Nmax = n + kb + p;
-  L.ld = 0;  // unused: the factor uses the packed-blocked layout of moff()
-  int o = 0;
-  auto take = [&](int cnt) { int r = o; o += al4(cnt > 0 ? cnt : 1); return r; };
-  L.x = take(n); L.y = take(p); L.z = take(m); L.s = take(m); L.v = take(m);
-  L.q = take(n); L.h = take(m); L.b = take(p);
-  L.E = take(m); L.D = take(m); L.c = take(m);
-  L.rt = take(n); L.ri = take(m); L.re = take(p); L.rz = take(m); L.rs = take(m);
-  L.tGz = take(n); L.tAy = take(n);
-  const int tlen = max(max(m, p), L.Nmax);  // t0/t1 also hold refinement rhs copies
-  L.t0 = take(tlen); L.t1 = take(tlen);
-  L.u0 = take(L.Nmax); L.u1 = take(L.Nmax);
-  L.dv0 = take(m); L.dv1 = take(m); L.dinv = take((L.Nmax + 15) & ~15);
-  // partial sums (2 floats or 1 double per thread) and reduction scratch
-  L.part = take(2 * T); L.red = take((T / 64) * 16);
-  L.w0 = L.t0; L.w1 = L.t1; L.rr = take(L.Nmax); L.rd = take(L.Nmax);
-  L.dd = take(2 * (2 * m + p + n + 8));
-  L.pan = take(4);
-  L.role = take(m); L.bidx = take(m); L.elist = take(m); L.iflag = take(16);
-  L.stg = L.u0;
-  L.stg_len = L.pan - L.u0;
+  const int sn = al4(n), sm = al4(max(m, 1)), sp = al4(max(p, 1)), sN = al4(L.Nmax);
+  const int st = al4(max(max(m, p), L.Nmax));  // t0, t1: also m- and p-vectors
+  L.iflag = 0;
+  // partial sums: 2 floats or 1 double per thread
+  L.part = 16; L.red = L.part + 2 * T;
+  const int b0 = L.red + (T / 64) * 16;
+  L.u0 = b0; L.u1 = b0 + sN; L.rr = b0 + 2 * sN; L.rd = b0 + 3 * sN;
+  L.dv0 = b0 + 4 * sN; L.dv1 = L.dv0 + sm;
+  L.dd = L.dv0 + 2 * sm;
+  L.dinv = L.dd + al4(2 * (2 * m + p + n + 8));
+  const int b1 = L.dinv + ((L.Nmax + 15) & ~15);
+  L.stg = L.part;
+  L.stg_len = b1 - L.part;
+  L.z = b1; L.s = b1 + sm; L.v = b1 + 2 * sm; L.h = b1 + 3 * sm; L.E = b1 + 4 * sm;
+  L.D = b1 + 5 * sm; L.c = b1 + 6 * sm; L.ri = b1 + 7 * sm; L.rz = b1 + 8 * sm;
+  L.rs = b1 + 9 * sm; L.role = b1 + 10 * sm; L.bidx = b1 + 11 * sm; L.elist = b1 + 12 * sm;
+  const int b2 = b1 + 13 * sm;
+  L.t0 = b2; L.t1 = b2 + st;
+  const int b3 = b2 + 2 * st;
+  L.x = b3; L.q = b3 + sn; L.rt = b3 + 2 * sn; L.tGz = b3 + 3 * sn; L.tAy = b3 + 4 * sn;
+  const int b4 = b3 + 5 * sn;
+  L.y = b4; L.b = b4 + sp; L.re = b4 + 2 * sp;
+  const int b5 = b4 + 3 * sp;
   // M's storage ends with 16 floats past the last row: a zero row for the
   // triangular solves, in M's own address space
-  if (m_lds) { L.M = o; o += al4(moff(L.Nmax) + kNB); } else { L.M = -1; }
-  L.total = o;
+  L.M = m_lds ? b5 : -1;
+  L.total = m_lds ? b5 + al4(moff(L.Nmax) + kNB) : b5;
   return L;
 }
 
 // ---------------------------------------------------------------------------
 // Dense helpers on one workgroup of T threads.
 
-// Columns jb + sub + 16q (q < 4) of row i of R (rows x cols, row stride
-// ld), loaded from clamped in-bounds addresses without a branch, so that
-// the loads of an unrolled row loop issue together; entries outside the
-// matrix read as 0.  Needs rows >= 1 and cols >= 1.
-template <class RF>
-QPD void load_row4(const RF *R, int ld, int rows, int cols, int i, int jb, int sub,
-                   float (&e)[4]) {
-  const bool in = i < rows;
-  const RF *Ri = R + (size_t)(in ? i : rows - 1) * ld;
+// Rows i0 + grp, i0 + grp + T/16, ... (U of them) of R, columns jb + sub +
+// 16 q: the loads only, from clamped in-bounds addresses (a use next to a load,
+// a select to mask it included, would wait for it).  Row batches past the last
+// row are skipped; rows and columns past the last hold entries of the last,
+// for the users to mask.
+template <int T, int U>
+QPD void load_rows(const gf *R, int ld, int rows, int cols, int i0, int jb, float (&e)[U][4]) {
+  const int sub = tidx() & 15, grp = tidx() >> 4;
+  int j[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = jb + sub + 16 * q;
-    const float v = Ri[min(j, cols - 1)];
-    e[q] = (in && j < cols) ? v : 0.f;
+  for (int q = 0; q < 4; ++q) j[q] = min(jb + sub + 16 * q, cols - 1);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (i0 + u * (T / 16) < rows) {
+      const int i = min(i0 + u * (T / 16) + grp, rows - 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[u][q] = R[(unsigned)(i * ld + j[q])];
+    }
   }
 }
 
 // out[i] = sum_j R[i*ld + j] x[j] for i < rows.  16 lanes share a row
 // (columns jb + sub + 16c, c < 4, in blocks of 64) and T/16 rows go at a
-// time; the row loop is unrolled so that the loads of several rows are in
-// flight before their arithmetic.
-template <int T, int NV, class RF>
+// time, the loads of U batches of rows before their arithmetic.
+template <int T, int U, int NV, class RF>
 QPD void rowdot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV],
                 lf *const (&out)[NV]) {
   const int sub = tidx() & 15, grp = tidx() >> 4;
@@ -384,39 +419,36 @@ QPD void rowdot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV
 #pragma unroll
       for (int k = 0; k < NV; ++k) xv[k][c] = j < cols ? x[k][j] : 0.f;
     }
-#pragma unroll 4
-    for (int i0 = 0; i0 < rows; i0 += T / 16) {
-      const int i = i0 + grp;
-      float e[4] = {0.f, 0.f, 0.f, 0.f};
-      if (i < rows) {
-        const RF *Ri = R + (size_t)i * ld + jb + sub;
+    for (int i0 = 0; i0 < rows; i0 += U * (T / 16)) {
+      float e[U][4];
+      load_rows<T, U>(R, ld, rows, cols, i0, jb, e);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (jb + sub + 16 * c < cols) e[c] = Ri[16 * c];
-      }
-      float acc[NV];
+      for (int u = 0; u < U; ++u) {
+        if (i0 + u * (T / 16) < rows) {
+          const int i = i0 + u * (T / 16) + grp;
+          float acc[NV];
 #pragma unroll
-      for (int k = 0; k < NV; ++k) {
-        acc[k] = 0.f;
+          for (int k = 0; k < NV; ++k) {
+            acc[k] = 0.f;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[k] = fmaf(e[c], xv[k][c], acc[k]);
-        acc[k] = row_bfly<OpSum>(acc[k]);
-      }
-      if (sub == 0 && i < rows) {
+            for (int c = 0; c < 4; ++c) acc[k] = fmaf(e[u][c], xv[k][c], acc[k]);
+            acc[k] = row_bfly<OpSum>(acc[k]);
+          }
+          if (sub == 0 && i < rows) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) out[k][i] = jb ? out[k][i] + acc[k] : acc[k];
+            for (int k = 0; k < NV; ++k) out[k][i] = jb ? out[k][i] + acc[k] : acc[k];
+          }
+        }
       }
     }
   }
 }
 
 // out[j] = sum_i R[i*ld + j] x[i] for j < cols.  The same lane layout as
-// rowdot (16 lanes per row, 4 columns each, T/16 rows at a time, several
-// rows' loads in flight); each lane sums its columns over its rows, then the
-// row groups are combined by shuffles inside a wave and through `part`
-// (2T floats) across waves.  Barriers inside; `x` must be visible to all
-// threads on entry.
-template <int T, int NV, class RF>
+// rowdot; each lane sums its columns over its rows, then the row groups are
+// combined by shuffles inside a wave and through `part` (2T floats) across
+// waves.  Barriers inside; `x` must be visible to all threads on entry.
+template <int T, int U, int NV, class RF>
 QPD void coldot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV],
                 lf *const (&out)[NV], lf *part) {
   static_assert(NV <= 2, "part holds two floats per thread");
@@ -427,24 +459,21 @@ QPD void coldot(const RF *R, int ld, int rows, int cols, const lf *const (&x)[NV
     for (int k = 0; k < NV; ++k)
 #pragma unroll
       for (int q = 0; q < 4; ++q) c[k][q] = 0.f;
-#pragma unroll 4
-    for (int i0 = 0; i0 < rows; i0 += T / 16) {
-      const int i = i0 + grp;
-      float e[4] = {0.f, 0.f, 0.f, 0.f}, w[NV];
+    for (int i0 = 0; i0 < rows; i0 += U * (T / 16)) {
+      float e[U][4];
+      load_rows<T, U>(R, ld, rows, cols, i0, jb, e);
 #pragma unroll
-      for (int k = 0; k < NV; ++k) w[k] = 0.f;
-      if (i < rows) {
-        const RF *Ri = R + (size_t)i * ld + jb + sub;
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * (T / 16) + grp;
+        if (i < rows) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (jb + sub + 16 * q < cols) e[q] = Ri[16 * q];
+          for (int k = 0; k < NV; ++k) {
+            const float w = x[k][i];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) w[k] = x[k][i];
+            for (int q = 0; q < 4; ++q) c[k][q] = fmaf(e[u][q], w, c[k][q]);
+          }
+        }
       }
-#pragma unroll
-      for (int k = 0; k < NV; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) c[k][q] = fmaf(e[q], w[k], c[k][q]);
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k)
@@ -506,60 +535,77 @@ QPD void tiles_to_rows(const f4v (&t)[4], float (&P)[kNB]) {
   }
 }
 
+// And back.
+QPD void rows_to_tiles(const float (&P)[kNB], f4v (&t)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float x0 = P[r], x1 = P[4 + r], x2 = P[8 + r], x3 = P[12 + r];
+    swap16(x0, x1);
+    swap16(x2, x3);
+    swap32(x0, x2);
+    swap32(x1, x3);
+    t[0][r] = x0; t[1][r] = x1; t[2][r] = x2; t[3][r] = x3;
+  }
+}
+
 // Tiles t[0 .. CNT-1] -= sum over panels k < np of L[block, k] sg L[panel, k]':
-// ra[u] and rb point at this lane's row of block u and of the panel's diagonal
-// block (+ 4g), whose 16-byte segment of panel k is 16 k floats further on.
-// Instruction q multiplies component q, so the four v_mfma_f32_16x16x4_f32
-// cover the 16 columns; each panel's sum is formed from zero and then
-// subtracted, in ascending order of k.  The segments of the next panel are
-// loaded while this one's products run.
+// oa[u] and ob are the places in M of this lane's row of block u and of the
+// panel's diagonal block (+ 4g), whose 16-byte segments of panel k are k sa[u]
+// and k sb floats further on.  Instruction q multiplies component q, so the
+// four v_mfma_f32_16x16x4_f32 cover the 16 columns; each panel's sum is formed
+// from zero and then subtracted, in ascending order of k.  The segments of the
+// next panel are loaded while this one's products run; the loops carry no
+// branches (after one, every load waits for all those in flight), so panels
+// whose columns all have sign +1 have a loop of their own (a factorisation of
+// 440 rows: 494K -> 448K cycles).  Two to six panels in flight, or the
+// subtraction one panel behind, took 461K to 503K.
 template <int CNT, class MF>
-QPD void update_tiles(const MF *const (&ra)[4], const MF *rb, int np, int npos, f4v (&t)[4]) {
+QPD void update_tiles(const MF *M, const int (&oa)[4], const int (&sa)[4], int ob, int sb, int np,
+                      int npos, f4v (&t)[4]) {
   typedef typename Vec4<const MF>::type CV4;
   const int g4 = 4 * ((tidx() & 63) >> 4);
-  constexpr int U = CNT == 1 ? 2 : 1;  // panels per step: two independent chains at least
-  f4v a[U][CNT], b[U];
-  auto load = [&](int k, int h) {
-    const int o = 16 * min(k, np - 1);
-    b[h] = *reinterpret_cast<CV4 *>(rb + o);
-#pragma unroll
-    for (int u = 0; u < CNT; ++u) a[h][u] = *reinterpret_cast<CV4 *>(ra[u] + o);
+  auto at = [&](int o) {
+    return *reinterpret_cast<CV4 *>(M + (std::is_same<MF, lf>::value ? o : (unsigned)o));
   };
+  f4v a[CNT], b = at(ob);
+  int o[CNT];
 #pragma unroll
-  for (int h = 0; h < U; ++h) load(h, h);
-#pragma unroll 1
-  for (int k = 0; k < np; k += U) {
-    f4v acc[U][CNT], bs[U], as[U][CNT];
+  for (int u = 0; u < CNT; ++u) {
+    o[u] = oa[u];
+    a[u] = at(o[u]);
+  }
+  auto step = [&](int k, auto mixed) {
+    f4v bs = b, as[CNT];
 #pragma unroll
-    for (int h = 0; h < U; ++h) {
-      bs[h] = b[h];
+    for (int u = 0; u < CNT; ++u) as[u] = a[u];
+    const int d = k + 1 < np ? 1 : 0;  // (the last panel's segments again)
+    ob += d * sb;
+    b = at(ob);
 #pragma unroll
-      for (int u = 0; u < CNT; ++u) as[h][u] = a[h][u];
-      load(k + U + h, h);
-      if (16 * (k + h) + kNB > npos) {  // some columns of the panel have sign -1
-        const int c0 = 16 * (k + h) + g4;
-        bs[h].x *= c0 + 0 < npos ? 1.f : -1.f;
-        bs[h].y *= c0 + 1 < npos ? 1.f : -1.f;
-        bs[h].z *= c0 + 2 < npos ? 1.f : -1.f;
-        bs[h].w *= c0 + 3 < npos ? 1.f : -1.f;
-      }
-#pragma unroll
-      for (int u = 0; u < CNT; ++u) acc[h][u] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < CNT; ++u) {
+      o[u] += d * sa[u];
+      a[u] = at(o[u]);
     }
+    if constexpr (decltype(mixed)::value) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bs[q] *= 16 * k + g4 + q < npos ? 1.f : -1.f;
+    }
+    f4v acc[CNT];
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) acc[u] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int h = 0; h < U; ++h)
+      for (int u = 0; u < CNT; ++u)
+        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bs[q], as[u][q], acc[u], 0, 0, 0);
 #pragma unroll
-        for (int u = 0; u < CNT; ++u)
-          acc[h][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bs[h][q], as[h][u][q], acc[h][u], 0, 0, 0);
-#pragma unroll
-    for (int h = 0; h < U; ++h)
-      if (k + h < np) {
-#pragma unroll
-        for (int u = 0; u < CNT; ++u) t[u] -= acc[h][u];
-      }
-  }
+    for (int u = 0; u < CNT; ++u) t[u] -= acc[u];
+  };
+  const int kp = min(np, npos >> 4);
+#pragma unroll 2
+  for (int k = 0; k < kp; ++k) step(k, std::false_type{});
+#pragma unroll 1
+  for (int k = kp; k < np; ++k) step(k, std::true_type{});
 }
 
 // Dynamic regularisation (dyn): a pivot sg*a_jj that is not above
@@ -744,10 +790,9 @@ QPD void store_row(MF *M, int i, int k0, const float (&P)[kNB]) {
 // is bit for bit the factor of the unscaled matrix wherever the scaled
 // tests decide as the unscaled ones would, and the factor with the scaled
 // tests' replacements otherwise.  The assembly computes e_i while it copies
-// the border rows and keeps it in the first float of row i's padding, the
-// per-wave maxima of e in flag[8 ..] (at most 8 waves).
+// the border rows and keeps it in ex[i] (the place of 1 / L[i][i], which is
+// computed after the factorisation), the per-wave maxima of e in flag[8 ..] (at most 8 waves).
 constexpr int kNoExp = -1000;
-QPD int mpad(int i) { return moff(i) + 16 * ((i >> 4) + 1); }
 template <int T>
 QPD int border_emax(const li *flag) {
   int e = kNoExp;
@@ -755,20 +800,18 @@ QPD int border_emax(const li *flag) {
   for (int w = 0; w < T / 64; ++w) e = max(e, flag[8 + w]);
   return e;
 }
-template <class MF>
-QPD int border_shift(const MF *M, int i, int emax) {
-  const int e = __float_as_int(M[mpad(i)]);
+QPD int border_shift(const lf *ex, int i, int emax) {
+  const int e = __float_as_int(ex[i]);
   return e == kNoExp ? 0 : min((emax - e) >> 1, 30);
 }
 // Exponent e_i of the squared norm ss (the same in all 16 lanes of row i's
-// group) into row i's padding (if store), and the thread's running maximum.
-template <class MF>
-QPD void border_exponent(MF *M, int i, bool store, int sub, float ss, float &el) {
+// group) into ex[i] (if store), and the thread's running maximum.
+QPD void border_exponent(lf *ex, int i, bool store, int sub, float ss, float &el) {
   ss = row_bfly<OpSum>(ss);
   int e = kNoExp;
   if (ss > 0.f && ss <= FLT_MAX) (void)frexpf(ss, &e);
   if (store) {
-    if (sub == 0) M[mpad(i)] = __int_as_float(e);
+    if (sub == 0) ex[i] = __int_as_float(e);
     el = fmaxf(el, (float)e);
   }
 }
@@ -782,12 +825,12 @@ QPD void border_exponents_done(float el, li *flag) {
 // Wave 0: f(i, k_i) for every border row i with k_i > 0, in row order (a
 // lane per row reads the exponents; the rows to rescale, usually few, are
 // then taken one at a time by the whole wave).
-template <class MF, class F>
-QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
+template <class F>
+QPD void border_shifted_rows(const lf *ex, int N, int npos, int emax, F &&f) {
   const int lane = tidx() & 63, K = N - npos;
   for (int k0 = 0; k0 < K; k0 += 64) {
     const int k = k0 + lane;
-    const int sh = k < K ? border_shift(M, npos + k, emax) : 0;
+    const int sh = k < K ? border_shift(ex, npos + k, emax) : 0;
     unsigned long long b = __ballot(sh > 0);
     while (b) {
       const int l = __builtin_ctzll(b);
@@ -817,7 +860,8 @@ QPD void border_shifted_rows(const MF *M, int N, int npos, int emax, F &&f) {
 // flag[8 ..]; flag[1] and flag[3] are left alone.  RPL = rows per lane,
 // >= ceil(N / 64).
 template <int T, int RPL, class MF>
-QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *dsh) {
+QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *dsh, lf *ex) {
+  ex = rflp(ex);
   M = rflp(M); N = opaque(rfl(N)); npos = opaque(rfl(npos)); flag = rflp(flag); dyn = rfl(dyn); dsh = rflp(dsh);
   constexpr int NW = T / 64;
   constexpr int kMaxBlk = 4 * RPL;            // 16-row blocks of the largest system
@@ -838,17 +882,17 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
   if (eq) {
     // (usually no row needs it; every wave looks)
     bool any = false;
-    for (int k = lane; k < N - npos; k += 64) any |= border_shift(M, npos + k, emax) > 0;
+    for (int k = lane; k < N - npos; k += 64) any |= border_shift(ex, npos + k, emax) > 0;
     eq = __any(any);
   }
   if (eq) {
     __syncthreads();  // every wave has looked
     if (wid == 0) {
-      border_shifted_rows(M, N, npos, emax, [&](int i, int sh) {
-        MF *row = M + moff(i);
+      border_shifted_rows(ex, N, npos, emax, [&](int i, int sh) {
+        const MRow<MF> row = mrow<MF>(N, i);
         const float s = ldexpf(1.f, sh);
-        for (int j = lane; j < npos; j += 64) row[j] *= s;
-        if (lane == 0) row[i] *= s * s;  // the border block is diagonal here
+        for (int j = lane; j < npos; j += 64) M[row.at(j)] *= s;
+        if (lane == 0) M[row.at(i)] *= s * s;  // the border block is diagonal here
       });
     }
     __syncthreads();
@@ -858,11 +902,15 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     const int k0 = kNB * p, kb = min(kNB, N - k0), below = nblk - 1 - p;
     // this lane's row of block q (clamped: rows past N-1 read row N-1 and are
     // not stored)
-    auto row_of = [&](int q) -> const MF * {
+    constexpr bool kLds = std::is_same<MF, lf>::value;
+    auto row_of = [&](int q, int &step) {
       const int r = min(c16, N - 1 - kNB * q);
-      return M + (moff(kNB * q) + r * (20 + kNB * q) + g4);
+      const MRow<MF> row = mrow<MF>(N, kNB * q);
+      step = row.step;
+      return row.base + r * (kLds ? 20 + kNB * q : kNB) + g4;
     };
-    const MF *rb = row_of(p);
+    int sb;
+    const int ob = row_of(p, sb);
     // slots of this wave: block p + j(s); wave 0's slot 0 is the diagonal
     // block, which the other waves get through dsh
     const int s0 = wid == 0 ? 0 : 1;
@@ -871,13 +919,13 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     f4v t[4];
     auto update = [&](auto cnt, auto first) {
       constexpr int CNT = decltype(cnt)::value;
-      const MF *ra[4];
+      int oa[4], sa[4];
 #pragma unroll
       for (int u = 0; u < CNT; ++u) {
-        ra[u] = row_of(p + first(u));
-        t[u] = *reinterpret_cast<CV4 *>(ra[u] + k0);
+        oa[u] = row_of(p + first(u), sa[u]);
+        t[u] = *reinterpret_cast<CV4 *>(M + oa[u] + p * sa[u]);
       }
-      if (p) update_tiles<CNT>(ra, rb, p, npos, t);
+      if (p) update_tiles<CNT>(M, oa, sa, ob, sb, p, npos, t);
     };
     auto update_n = [&](int cnt, auto first) {
       if (cnt == 1) update(std::integral_constant<int, 1>{}, first);
@@ -911,10 +959,28 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
 #pragma unroll
         for (int c = 1; c < kNB; ++c) P[c] = lane < c ? 0.f : P[c];  // right of the diagonal
       }
-      {
-        const int j = block_of(sl), i = kNB * (p + j) + c16;
-        if ((wid == 0 || sl > 0) && j <= below && i < N) store_row(M, i, k0, P);
-      }
+      // slots s0 .. : block p + first(s)
+      auto store = [&](const float (&R)[kNB], int from, auto first) {
+        if constexpr (kLds) {
+          const int j = first(sl), i = kNB * (p + j) + c16;
+          if (sl >= from && j <= below && i < N) store_row(M, i, k0, R);
+        } else {
+          typedef typename Vec4<MF>::type V4;
+          f4v o[4];
+          rows_to_tiles(R, o);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int j = first(s);
+            if (s >= from && j <= below) {
+              int step;
+              MF *d = M + row_of(p + j, step);
+              d += p * step;
+              if (kNB * (p + j) + c16 < N) *reinterpret_cast<V4 *>(d) = o[s];
+            }
+          }
+        }
+      };
+      store(P, s0, block_of);
       if constexpr (kMore) {
         // blocks past the waves' first slots, four per wave at a time
 #pragma unroll 1
@@ -924,8 +990,7 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
           float R[kNB];
           tiles_to_rows(t, R);
           eliminate_more(R, P, iv, k0, kb, npos);
-          const int j = j0 + NW * sl, i = kNB * (p + j) + c16;
-          if (j <= below && i < N) store_row(M, i, k0, R);
+          store(R, 0, [&](int s) { return j0 + NW * s; });
         }
       }
     }
@@ -946,9 +1011,9 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     // report a failure so the caller factors again with a uniform floor
     float lmax = 0.f;
     for (int i = wid; i < N; i += NW) {
-      const MF *row = M + moff(i);
+      const MRow<MF> row = mrow<MF>(N, i);
       for (int j = lane; j <= i; j += 64) {
-        const float v = fabsf(row[j]);
+        const float v = fabsf(M[row.at(j)]);
         lmax = v <= FLT_MAX ? fmaxf(lmax, v) : __int_as_float(0x7f800000);
       }
     }
@@ -960,10 +1025,10 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
   }
   if (eq) {
     if (wid == 0) {
-      border_shifted_rows(M, N, npos, emax, [&](int i, int sh) {
-        MF *row = M + moff(i);
+      border_shifted_rows(ex, N, npos, emax, [&](int i, int sh) {
+        const MRow<MF> row = mrow<MF>(N, i);
         const float r = ldexpf(1.f, -sh);
-        for (int j = lane; j <= i; j += 64) row[j] *= r;
+        for (int j = lane; j <= i; j += 64) M[row.at(j)] *= r;
       });
     }
     __syncthreads();
@@ -1129,7 +1194,8 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r,
   for (int b = nblk - 1; b >= 0; --b) {
     const int l0 = (kNB / S) * (b / WG);
     const bool own = WG == 1 || b % WG == g;
-    lf *e = ex + 16 * (b & 1);
+    // (not the buffer of the forward sweep's last step: it may still be read)
+    lf *e = ex + 16 * ((b & 1) ^ 1);
     if (own) {
 #pragma unroll
       for (int h = kNB - CW; h >= 0; h -= CW) {
@@ -1164,18 +1230,184 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r,
     if (i0 + t < N) r[i0 + t] = a[t];
 }
 
-// The solves of one or two right-hand sides side by side: up to 4 rows per
-// lane one wave each (the chain of dependent steps bounds them), above that
-// half of the workgroup's waves each.  A barrier must follow.
+// The same solve, of one or two right-hand sides, with a factor in global
+// memory (16x16 tiles), by all T/64 = NW waves of the workgroup.  Blocks are
+// dealt to the waves in turn; lane 16 s + c holds row c of the wave's local
+// blocks 4 t + s (register t), for both right-hand sides, so that a tile of
+// the factor is read once, as one run.  The forward sweep transposes the
+// tiles it reads into a row per lane (tiles_to_rows), the backward sweep reads
+// rows of 16 tiles with a column per lane.  Per block: its owner's 16
+// dependent steps, the values passed on through `ex` (64 floats, two buffers
+// taken in turn), one barrier, and the other waves' subtractions.  One wave per
+// right-hand side, each reading the factor with a row per lane, spent 7K
+// cycles per block on the 64 cache lines of every load (n = 256); this takes
+// about 1K.
+template <int T, int RPL>
+QPD void signed_solve_tiles(const gf *M, int N, int npos, const lf *dinv, lf *r0, lf *r1,
+                            bool both, lf *ex) {
+  constexpr int NW = T / 64, S = RPL > NW ? RPL / NW : 1;
+  const int lane = tidx() & 63, g = rfl(tidx() >> 6), c16 = lane & 15, sl = lane >> 4;
+  const int nblk = (N + 15) >> 4, last = nblk - 1;
+  float a[2][S], dl[S];
+  int qi[S];  // this lane's blocks
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    qi[t] = (4 * t + sl) * NW + g;
+    const int i = kNB * qi[t] + c16;
+    const bool in = i < N;
+    a[0][t] = in ? r0[min(i, N - 1)] : 0.f;
+    a[1][t] = in && both ? r1[min(i, N - 1)] : 0.f;
+    dl[t] = in ? dinv[min(i, N - 1)] : 0.f;
+  }
+  f4v nt[S][4];
+  // this lane's place in a tile (rows of the last tile row that do not exist
+  // read its last one)
+  const unsigned po = 16 * c16 + 4 * sl;
+  const unsigned pl = 16 * min(c16, N - 1 - kNB * last) + 4 * sl;
+  auto load_f = [&](int b) {  // panel b of this wave's blocks
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = (4 * t + u) * NW + g;
+        nt[t][u] = f4v{0.f, 0.f, 0.f, 0.f};  // finished blocks
+        if (q >= b && q < nblk) {
+          const MRow<gf> row = mrow<gf>(N, kNB * q);
+          const gf *tile = M + (row.base + b * row.step);
+          nt[t][u] = *reinterpret_cast<const gf4 *>(tile + (q == last ? pl : po));
+        }
+      }
+  };
+  float Lc[S][kNB];
+  // the owner's steps on its block in register to, lanes l0 .. l0+15 (rows
+  // past the last one hold 0)
+  auto chain = [&](auto tc, int l0, auto upc) {
+    constexpr int to = decltype(tc)::value;
+    constexpr bool up = decltype(upc)::value;
+    a[0][to] = kNB * qi[to] + c16 < N ? a[0][to] : 0.f;
+    a[1][to] = kNB * qi[to] + c16 < N ? a[1][to] : 0.f;
+#pragma unroll
+    for (int k = 0; k < kNB; ++k) {
+      const int c = up ? k : kNB - 1 - k;
+      const float w0 = a[0][to] * dl[to], w1 = a[1][to] * dl[to];
+      const float x0 = readlane(w0, l0 + c), x1 = readlane(w1, l0 + c);
+      a[0][to] = fmaf(-Lc[to][c], x0, a[0][to]);
+      a[1][to] = fmaf(-Lc[to][c], x1, a[1][to]);
+      const bool me = lane == l0 + c;
+      a[0][to] = me ? w0 : a[0][to];
+      a[1][to] = me ? w1 : a[1][to];
+    }
+  };
+  auto step = [&](int b, auto upc) {
+    constexpr bool up = decltype(upc)::value;
+    // the buffer after the last step's: down from the last block it is the
+    // other one of the pair (its readers passed that block's barrier)
+    lf *e = ex + 32 * ((b & 1) ^ (up ? 0 : 1));
+    const int lb = b / NW, to = lb >> 2, l0 = 16 * (lb & 3);
+    const bool own = b % NW == g;
+    if (own) {
+#pragma unroll
+      for (int t = 0; t < S; ++t)
+        if (t == to) {
+          if (t == 0) chain(std::integral_constant<int, 0>{}, l0, upc);
+          if constexpr (S > 1)
+            if (t == 1) chain(std::integral_constant<int, 1>{}, l0, upc);
+          if constexpr (S > 2)
+            if (t == 2) chain(std::integral_constant<int, 2>{}, l0, upc);
+          if constexpr (S > 3)
+            if (t == 3) chain(std::integral_constant<int, 3>{}, l0, upc);
+          if (lane >= l0 && lane < l0 + kNB) {
+            e[lane - l0] = a[0][t];
+            e[kNB + lane - l0] = a[1][t];
+          }
+        }
+    }
+    __syncthreads();
+    if (S > 1 || !own) {
+      f4v x0[4], x1[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        x0[k] = *reinterpret_cast<const lf4 *>(e + 4 * k);
+        x1[k] = *reinterpret_cast<const lf4 *>(e + kNB + 4 * k);
+      }
+#pragma unroll
+      for (int t = 0; t < S; ++t) {
+        if (!own || t != to) {
+#pragma unroll
+          for (int k = 0; k < kNB; ++k) {
+            const int c = up ? k : kNB - 1 - k;
+            a[0][t] = fmaf(-Lc[t][c], x0[c >> 2][c & 3], a[0][t]);
+            a[1][t] = fmaf(-Lc[t][c], x1[c >> 2][c & 3], a[1][t]);
+          }
+        }
+      }
+    }
+  };
+  static_assert(S <= 4, "owner registers");
+  load_f(0);
+#pragma unroll 1
+  for (int b = 0; b < nblk; ++b) {
+#pragma unroll
+    for (int t = 0; t < S; ++t) tiles_to_rows(nt[t], Lc[t]);
+    load_f(min(b + 1, last));
+    step(b, std::true_type{});
+  }
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+    if (kNB * qi[t] + c16 >= npos) {
+      a[0][t] = -a[0][t];
+      a[1][t] = -a[1][t];
+    }
+  float nx[S][kNB];
+  auto load_b = [&](int b) {  // rows 16 b .. at this lane's columns
+    const MRow<gf> row = mrow<gf>(N, kNB * b);
+    const int rows = b == last ? N - kNB * last : kNB;
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+      // (zeros right of the diagonal in block b itself; rows past the last
+      // read it again: their values are 0)
+      const unsigned o = row.base + min(qi[t], b) * row.step + c16;
+#pragma unroll
+      for (int c = 0; c < kNB; ++c) nx[t][c] = M[o + 16 * min(c, rows - 1)];
+    }
+  };
+  load_b(last);
+#pragma unroll 1
+  for (int b = last; b >= 0; --b) {
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+#pragma unroll
+      for (int c = 0; c < kNB; ++c) Lc[t][c] = qi[t] <= b ? nx[t][c] : 0.f;
+    load_b(max(b - 1, 0));
+    step(b, std::false_type{});
+  }
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = kNB * qi[t] + c16;
+    if (i < N) {
+      r0[i] = a[0][t];
+      if (both) r1[i] = a[1][t];
+    }
+  }
+}
+
+// The solves of one or two right-hand sides side by side.  With the factor in
+// LDS, up to 4 rows per lane one wave each (the chain of dependent steps
+// bounds them), above that half of the workgroup's waves each.  A barrier must
+// follow.
 template <int T, int RPL, class MF>
 QPD void signed_solve(const MF *M, int N, int npos, const lf *dinv, lf *r0, lf *r1, bool both,
                       const MF *zrow, lf *ex) {
-  constexpr int WG = RPL > 4 ? T / 128 : 1, S = RPL / WG;
-  const int wid = rfl(tidx() >> 6), k = wid / WG;
-  if (k == 0 || (k == 1 && both)) {
-    signed_solve_waves<S, WG>(M, N, npos, dinv, k ? r1 : r0, zrow, wid % WG, ex + 32 * k);
-  } else if constexpr (WG > 1) {
-    for (int b = 2 * ((N + 15) >> 4); b > 0; --b) __syncthreads();
+  if constexpr (std::is_same<MF, lf>::value) {
+    constexpr int WG = RPL > 4 ? T / 128 : 1, S = RPL / WG;
+    const int wid = rfl(tidx() >> 6), k = wid / WG;
+    if (k == 0 || (k == 1 && both)) {
+      signed_solve_waves<S, WG>(M, N, npos, dinv, k ? r1 : r0, zrow, wid % WG, ex + 32 * k);
+    } else if constexpr (WG > 1) {
+      for (int b = 2 * ((N + 15) >> 4); b > 0; --b) __syncthreads();
+    }
+  } else {
+    signed_solve_tiles<T, RPL>(M, N, npos, dinv, r0, r1, both, ex);
   }
 }
 
@@ -1221,7 +1453,7 @@ QPD float coldot_d(const RF *R, int ld, int rows, int cols, const XF *x,
 // mq, mg, ma (per-thread partial maxima).  Without gcols, G contributes
 // its row dots only (z is not read).  No LDS pointer is tested against
 // NULL: LDS address 0 is a valid address.  Barriers inside.
-template <int T, class AT>
+template <int T, int U, class AT>
 QPD void kkt_matvecs(const gf *Q, const gf *G, const gf *A, int n, int m, int p, const lf *x,
                      const lf *z, bool gcols, const lf *y, typename LdsT<AT>::type *gx,
                      typename LdsT<AT>::type *ax, typename LdsT<AT>::type *rt,
@@ -1242,27 +1474,26 @@ QPD void kkt_matvecs(const gf *Q, const gf *G, const gf *A, int n, int m, int p,
     // with x into out
     auto sweep = [&](const gf *R, int rows, const lf *w, bool cols, la *out, bool dots,
                      AT(&c)[4]) {
-#pragma unroll 4
-      for (int i0 = 0; i0 < rows; i0 += RG) {
-        const int i = i0 + grp;
-        float e[4] = {0.f, 0.f, 0.f, 0.f};
-        AT wi = 0;
-        if (i < rows) {
-          const gf *Ri = R + (size_t)i * n + jb + sub;
+          for (int i0 = 0; i0 < rows; i0 += U * RG) {
+        float e[U][4];
+        load_rows<T, U>(R, n, rows, n, i0, jb, e);
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (jb + sub + 16 * k < n) e[k] = Ri[16 * k];
-          if (cols) wi = (AT)w[i];
-        }
-        AT d = 0;
+        for (int u = 0; u < U; ++u) {
+          if (i0 + u * RG < rows) {
+            const int i = i0 + u * RG + grp;
+            const bool in = i < rows;
+            const AT wi = cols && in ? (AT)w[i] : (AT)0;
+            AT d = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          c[k] = fma((AT)e[k], wi, c[k]);
-          if (dots) d = fma((AT)e[k], xv[k], d);
-        }
-        if (dots) {
-          d = row_bfly<OpSum>(d);
-          if (sub == 0 && i < rows) out[i] = jb ? out[i] + d : d;
+            for (int k = 0; k < 4; ++k) {
+              if (in) c[k] = fma((AT)e[u][k], wi, c[k]);
+              if (dots) d = fma((AT)e[u][k], xv[k], d);
+            }
+            if (dots) {
+              d = row_bfly<OpSum>(d);
+              if (sub == 0 && in) out[i] = jb ? out[i] + d : d;
+            }
+          }
         }
       }
     };
@@ -1298,72 +1529,31 @@ QPD void kkt_matvecs(const gf *Q, const gf *G, const gf *A, int n, int m, int p,
 // ---------------------------------------------------------------------------
 // The per-QP context: LDS views plus this QP's global problem data.
 //
-// The addresses of the views live in a small table in LDS (one per
-// workgroup, written once per QP), not in the context object: each use
-// reads its entry back (a broadcast LDS load, made uniform), so no address
-// stays live in registers from one phase to the next.  Kept live, the
-// fifty-odd addresses overflow the scalar register file and are spilled and
-// reloaded one by one at every phase entry.  Global addresses take two
-// words.
-enum CtxSlot {
-  CS_X, CS_Y, CS_Z, CS_S, CS_V, CS_Q, CS_H, CS_B, CS_E, CS_D, CS_C,
-  CS_RT, CS_RI, CS_RE, CS_RZ, CS_RS, CS_TGZ, CS_TAY,
-  CS_T0, CS_T1, CS_U0, CS_U1, CS_DV0, CS_DV1, CS_DINV, CS_PART, CS_RED,
-  CS_W0, CS_W1, CS_RR, CS_RD, CS_PAN, CS_DD, CS_ROLE, CS_BIDX, CS_ELIST, CS_IFLAG, CS_STG,
-  CS_M = 40, CS_MZ = 42, CS_GQ = 44, CS_GQV = 46, CS_GA = 48, CS_GB = 50, CS_GG = 52,
-  CS_GH = 54, CS_N = 56
-};
-static __shared__ unsigned qpk_ctab[CS_N];
-static_assert(CS_N * 4 <= kStaticLds, "static LDS bound of the launch planning");
-
-// A context address: reads entry K of the table (PT carries the address
-// space, 32-bit LDS or 64-bit global addresses).
-template <class PT, int K>
-struct CtxRef {
-  QPD PT *get() const {
-    if constexpr (sizeof(PT *) == 4) {
-      return (PT *)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)qpk_ctab[K]);
-    } else {
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)qpk_ctab[K]);
-      const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)qpk_ctab[K + 1]);
-      return (PT *)(uintptr_t)(((uint64_t)hi << 32) | lo);
-    }
-  }
-  QPD operator PT *() const { return get(); }
-  // by one thread; a barrier must follow before any use
-  QPD void set(PT *a) const {
-    const uint64_t v = (uint64_t)(uintptr_t)a;
-    qpk_ctab[K] = (uint32_t)v;
-    if constexpr (sizeof(PT *) == 8) qpk_ctab[K + 1] = (uint32_t)(v >> 32);
-  }
-};
-
-template <class MF>
+// Each phase makes its own copy (uctx), whose LDS addresses are computed from
+// opaque copies of the sizes, so none stays live from one phase to the next
+// (kept live, the fifty-odd addresses overflow the scalar register file) and
+// those that a phase does not use cost nothing.  Read back from a table in LDS
+// instead, every phase began with a chain of LDS loads.
+template <int T_, int RPL, class MF>
 struct Ctx {
   typedef MF MT;
+  static constexpr int T = T_;
+  // row batches in flight in the products with Q, G and A: eight from 4 rows
+  // per lane on (1024 QPs of n = 100, forward and backward: 9.3 -> 8.2 ms);
+  // below, their registers spill (1 QP of n = 8: 234 -> 250 us)
+  static constexpr int U = RPL >= 4 ? 8 : 4;
   int n, m, p, kb;
-  CtxRef<const gf, CS_GQ> Q;
-  CtxRef<const gf, CS_GQV> q_g;
-  CtxRef<const gf, CS_GA> A;
-  CtxRef<const gf, CS_GB> b_g;
-  CtxRef<const gf, CS_GG> G;
-  CtxRef<const gf, CS_GH> h_g;
-  CtxRef<MF, CS_M> M;    // factor storage (LDS or global)
-  CtxRef<lf, CS_X> x; CtxRef<lf, CS_Y> y; CtxRef<lf, CS_Z> z; CtxRef<lf, CS_S> s;
-  CtxRef<lf, CS_V> v; CtxRef<lf, CS_Q> q; CtxRef<lf, CS_H> h; CtxRef<lf, CS_B> b;
-  CtxRef<lf, CS_E> E; CtxRef<lf, CS_D> D; CtxRef<lf, CS_C> c;
-  CtxRef<lf, CS_RT> rt; CtxRef<lf, CS_RI> ri; CtxRef<lf, CS_RE> re; CtxRef<lf, CS_RZ> rz;
-  CtxRef<lf, CS_RS> rs; CtxRef<lf, CS_TGZ> tGz; CtxRef<lf, CS_TAY> tAy;
-  CtxRef<lf, CS_T0> t0; CtxRef<lf, CS_T1> t1; CtxRef<lf, CS_U0> u0; CtxRef<lf, CS_U1> u1;
-  CtxRef<lf, CS_DV0> dv0; CtxRef<lf, CS_DV1> dv1; CtxRef<lf, CS_DINV> dinv;
-  CtxRef<lf, CS_PART> part; CtxRef<lf, CS_RED> red;
-  CtxRef<lf, CS_W0> w0; CtxRef<lf, CS_W1> w1; CtxRef<lf, CS_RR> rr; CtxRef<lf, CS_RD> rd;
-  CtxRef<lf, CS_PAN> pan;
-  CtxRef<MF, CS_MZ> mz;  // 16 zeros after M's last row (same address space as M)
-  CtxRef<ldd, CS_DD> dd;
-  CtxRef<li, CS_ROLE> role; CtxRef<li, CS_BIDX> bidx; CtxRef<li, CS_ELIST> elist;
-  CtxRef<li, CS_IFLAG> iflag;
-  CtxRef<lf, CS_STG> stg;  // matrix-core assembly staging (aliases u0 .. dd)
+  const gf *Q, *q_g, *A, *b_g, *G, *h_g;
+  MF *Mg;  // factor storage when it is global
+  MF *M;   // factor storage (LDS or global)
+  lf *x, *y, *z, *s, *v, *q, *h, *b, *E, *D, *c;
+  lf *rt, *ri, *re, *rz, *rs, *tGz, *tAy;
+  lf *t0, *t1, *u0, *u1, *dv0, *dv1, *dinv, *part, *red;
+  lf *w0, *w1, *rr, *rd;  // w0, w1: rhs copies of the refinement (in t0, t1)
+  MF *mz;  // 16 zeros after M's last row (same address space as M)
+  ldd *dd;
+  li *role, *bidx, *elist, *iflag;
+  lf *stg;  // matrix-core assembly staging (aliases part .. dinv)
   int amode;  // H-block assembly: 0 FP32 VALU, 1 BF16x3 MFMA, 2 FP32 MFMA
   int dyn;    // bounded form: regularise degenerate factorisations (R13)
   int rmode;  // residual precision: 0 FP32 first (FP64 refinement after a
@@ -1371,47 +1561,41 @@ struct Ctx {
   float bo;   // line-search back-off factor (1 = none)
 };
 
-// Sizes and scalar settings of the context, and (thread 0) the address
-// table; the caller's next barrier publishes the table.
-template <class MF>
-QPD void init_ctx(Ctx<MF> &C, lf *sm, const Layout &L, MF *Mptr, const gf *Qg, const gf *qg,
-                  const gf *Ag, const gf *bg, const gf *Gg, const gf *hg) {
-  C.n = L.n; C.m = L.m; C.p = L.p; C.kb = L.kb;
-  if (tidx() == 0) {
-    C.Q.set(Qg); C.q_g.set(qg); C.A.set(Ag); C.b_g.set(bg); C.G.set(Gg); C.h_g.set(hg);
-    C.M.set(Mptr);
-    C.x.set(sm + L.x); C.y.set(sm + L.y); C.z.set(sm + L.z); C.s.set(sm + L.s);
-    C.v.set(sm + L.v); C.q.set(sm + L.q); C.h.set(sm + L.h); C.b.set(sm + L.b);
-    C.E.set(sm + L.E); C.D.set(sm + L.D); C.c.set(sm + L.c);
-    C.rt.set(sm + L.rt); C.ri.set(sm + L.ri); C.re.set(sm + L.re); C.rz.set(sm + L.rz);
-    C.rs.set(sm + L.rs); C.tGz.set(sm + L.tGz); C.tAy.set(sm + L.tAy);
-    C.t0.set(sm + L.t0); C.t1.set(sm + L.t1); C.u0.set(sm + L.u0); C.u1.set(sm + L.u1);
-    C.dv0.set(sm + L.dv0); C.dv1.set(sm + L.dv1); C.dinv.set(sm + L.dinv);
-    C.part.set(sm + L.part); C.red.set(sm + L.red);
-    C.w0.set(sm + L.w0); C.w1.set(sm + L.w1); C.rr.set(sm + L.rr); C.rd.set(sm + L.rd);
-    C.pan.set(sm + L.pan);
-    C.mz.set(Mptr + moff(L.Nmax));
-    C.dd.set(reinterpret_cast<ldd *>(sm + L.dd));
-    C.role.set(reinterpret_cast<li *>(sm + L.role));
-    C.bidx.set(reinterpret_cast<li *>(sm + L.bidx));
-    C.elist.set(reinterpret_cast<li *>(sm + L.elist));
-    C.iflag.set(reinterpret_cast<li *>(sm + L.iflag));
-    C.stg.set(sm + L.stg);
-  }
-  C.amode = 0;
-  C.dyn = 1;
-  C.rmode = 0;
-  C.bo = 1.f;
+extern __shared__ __attribute__((aligned(16))) float qpk_smem[];
+
+// Addresses of the context's LDS views from its sizes.
+template <class CT>
+QPD void place(CT &C) {
+  constexpr bool mlds = std::is_same<typename CT::MT, lf>::value;
+  const Layout L = make_layout(C.n, C.m, C.p, C.kb, mlds, CT::T);
+  lf *sm = (lf *)qpk_smem;
+  C.x = sm + L.x; C.y = sm + L.y; C.z = sm + L.z; C.s = sm + L.s; C.v = sm + L.v;
+  C.q = sm + L.q; C.h = sm + L.h; C.b = sm + L.b; C.E = sm + L.E; C.D = sm + L.D;
+  C.c = sm + L.c; C.rt = sm + L.rt; C.ri = sm + L.ri; C.re = sm + L.re; C.rz = sm + L.rz;
+  C.rs = sm + L.rs; C.tGz = sm + L.tGz; C.tAy = sm + L.tAy; C.t0 = sm + L.t0; C.t1 = sm + L.t1;
+  C.u0 = sm + L.u0; C.u1 = sm + L.u1; C.dv0 = sm + L.dv0; C.dv1 = sm + L.dv1;
+  C.dinv = sm + L.dinv; C.part = sm + L.part; C.red = sm + L.red;
+  C.w0 = C.t0; C.w1 = C.t1; C.rr = sm + L.rr; C.rd = sm + L.rd;
+  C.dd = reinterpret_cast<ldd *>(sm + L.dd);
+  C.role = reinterpret_cast<li *>(sm + L.role);
+  C.bidx = reinterpret_cast<li *>(sm + L.bidx);
+  C.elist = reinterpret_cast<li *>(sm + L.elist);
+  C.iflag = reinterpret_cast<li *>(sm + L.iflag);
+  C.stg = sm + L.stg;
+  if constexpr (mlds) C.M = sm + L.M;
+  else C.M = C.Mg;
+  C.mz = C.M + moff(L.Nmax);
 }
 
-
-// Uniform copy of a context (see rfl): the sizes and settings; the
-// addresses are read from the table where they are used.
-template <class MF>
-QPD Ctx<MF> uctx(const Ctx<MF> &I) {
-  Ctx<MF> C;
+// Uniform copy of a context (see rfl) with its addresses.
+template <class CT>
+QPD CT uctx(const CT &I) {
+  CT C;
   C.n = opaque(rfl(I.n)); C.m = opaque(rfl(I.m)); C.p = opaque(rfl(I.p)); C.kb = opaque(rfl(I.kb));
+  C.Q = rflp(I.Q); C.q_g = rflp(I.q_g); C.A = rflp(I.A); C.b_g = rflp(I.b_g);
+  C.G = rflp(I.G); C.h_g = rflp(I.h_g); C.Mg = rflp(I.Mg);
   C.amode = rfl(I.amode); C.dyn = rfl(I.dyn); C.rmode = rfl(I.rmode); C.bo = rflf(I.bo);
+  place(C);
   return C;
 }
 
@@ -1432,13 +1616,13 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
   const int n = C.n, m = C.m, p = C.p, tid = tidx();
   // one accumulator for Qx + G'z + A'y; the pieces' norms are taken as they
   // are produced
-  la *gxd = reinterpret_cast<la *>(C.dd.get()), *axd = gxd + m, *rtd = gxd + m + p;
-  la *pd = reinterpret_cast<la *>(C.part.get());
+  la *gxd = reinterpret_cast<la *>(C.dd), *axd = gxd + m, *rtd = gxd + m + p;
+  la *pd = reinterpret_cast<la *>(C.part);
   enum { RT, QX, QQ, GZ, AY, RI, GX, SS, HH, RE, AX, BB, RZS, ZZ, CC, NF, NK };
   float mx[NK];
 #pragma unroll
   for (int k = 0; k < NK; ++k) mx[k] = 0.f;
-  kkt_matvecs<T, AT>(C.Q, C.G, C.A, n, m, p, C.x, C.z, true, C.y, gxd, axd, rtd, pd, mx[QX],
+  kkt_matvecs<T, CT::U, AT>(C.Q, C.G, C.A, n, m, p, C.x, C.z, true, C.y, gxd, axd, rtd, pd, mx[QX],
                      mx[GZ], mx[AY]);
   QPK_PT(PH_MATVEC);
   const bool man = bounded && kr > 0.f;  // relaxation of an implicit form
@@ -1529,7 +1713,7 @@ QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
   kappa = rflf(kappa);
   const int m = C.m, kb = C.kb, tid = tidx(), lane = tid & 63, w = tid >> 6;
   constexpr int NW = T / 64;
-  li *ws = reinterpret_cast<li *>(C.red.get());  // per-wave counts [2][NW]
+  li *ws = reinterpret_cast<li *>(C.red);  // per-wave counts [2][NW]
   const unsigned long long below = (1ull << lane) - 1ull;
   // One sweep: retraction derivatives, and the border / eliminated lists in
   // row order from wave ballots (the common case: at most kb rows with v > 0)
@@ -1581,7 +1765,7 @@ QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
     // ahead of it; v is read four rows per 16-byte broadcast load, several
     // loads in flight, and the padding past row m is masked.
     li *cand = C.role;
-    const lf4 *v4 = reinterpret_cast<const lf4 *>(C.v.get());
+    const lf4 *v4 = reinterpret_cast<const lf4 *>(C.v);
     const int m4 = (m + 3) >> 2;
     for (int i = tid; i < m; i += T) {
       int f = 0;
@@ -1639,7 +1823,6 @@ QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
 // 16..19 pad the record to 80 bytes, which spreads the 16 columns a
 // fragment load touches over the LDS banks.
 constexpr int kStgRec = 20;
-constexpr int kAsmTiles = 9;
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) unsigned lu;
 
@@ -1651,18 +1834,28 @@ QPD unsigned bf16_pair(float a, float b) {
 // LDS floats the matrix-core assembly stages for n columns.
 __host__ __device__ inline int stage_floats(int n) { return ((n + 15) & ~15) * kStgRec; }
 
+// The rows of a chunk are dealt to the waves in pairs (so that a row's address
+// and weight are scalars) and loaded one chunk ahead, while the products of the
+// present one run; a wave owns every tile it can in one pass (17 at 512 threads
+// take n = 256 in one: with 9, G was staged twice).  The square roots of the
+// weights are taken once per row, in row order.
 template <int T, class CT>
-QPD void assemble_h_mfma(CT &C, int ne, const lf *wts) {
+QPD void assemble_h_mfma(CT &C, int N, int ne, const lf *wts) {
   constexpr int W = T / 64;
-  const int n = C.n, tid = tidx(), lane = tid & 63, wid = tid >> 6;
+  constexpr int kAsmTiles = T >= 512 ? 17 : 9;
+  constexpr int kPairs = 8 / W > 0 ? 8 / W : 1;  // row pairs per wave
+  constexpr int kCols = T >= 512 ? 4 : 2;        // 64-column blocks loaded ahead
+  const int n = C.n, tid = tidx(), lane = tid & 63, wid = rfl(tid >> 6);
   const int n16 = (n + 15) & ~15, nt = n16 >> 4;
   const int ntl = nt * (nt + 1) / 2;
   const int passes = (ntl + W * kAsmTiles - 1) / (W * kAsmTiles);
   const int tpw = (ntl + passes * W - 1) / (passes * W);
   const bool bf = C.amode == 1;
   const int g = lane >> 4, c16 = lane & 15;
-  lf *stg = C.stg;
-  auto *M = C.M.get();
+  lf *stg = C.stg, *sw = C.t0;
+  auto *M = C.M;
+  for (int k = tid; k < ne; k += T) sw[k] = sqrtf(wts[C.elist[k]]);
+  __syncthreads();
   for (int pass = 0; pass < passes; ++pass) {
     int ti[kAsmTiles], tj[kAsmTiles];
     bool val[kAsmTiles];
@@ -1672,37 +1865,67 @@ QPD void assemble_h_mfma(CT &C, int ne, const lf *wts) {
       const int t = (pass * W + wid) * tpw + j;
       val[j] = j < tpw && t < ntl;
       ti[j] = tj[j] = 0;
-      if (val[j]) tile_ij(t, ti[j], tj[j]);
+      if (val[j]) {
+        tile_ij(t, ti[j], tj[j]);
+        ti[j] = rfl(ti[j]);
+        tj[j] = rfl(tj[j]);
+      }
       acc[j] = f4v{0.f, 0.f, 0.f, 0.f};
     }
-    for (int k0 = 0; k0 < ne; k0 += 16) {
-      __syncthreads();  // the previous chunk has been consumed
-      // stage rows k0 .. k0+15 of Y; item e covers rows 2kp, 2kp+1 of column c
-      for (int e = tid; e < 8 * n16; e += T) {
-        const int kp = e / n16, c = e - kp * n16;
-        float y0 = 0.f, y1 = 0.f;
-        const int k = k0 + 2 * kp;
-        if (c < n) {
-          if (k < ne) {
-            const int r = C.elist[k];
-            y0 = sqrtf(wts[r]) * C.G[(size_t)r * n + c];
+    // rows 2 kp, 2 kp + 1 of the chunk at k0, kp = wid + W i, this lane's
+    // columns cb + lane + 64 q
+    float y[kPairs][kCols][2];
+    auto load = [&](int k0, int cb) {
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        const int k = k0 + 2 * (wid + W * i);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool in = wid + W * i < 8 && k + h < ne;
+          const gf *row = C.G + (size_t)rfl(C.elist[in ? k + h : 0]) * n;
+          const float w = in ? rflf(sw[k + h]) : 0.f;
+#pragma unroll
+          for (int q = 0; q < kCols; ++q) {
+            const int c = cb + lane + 64 * q;
+            y[i][q][h] = in && c < n ? w * row[c] : 0.f;
           }
-          if (k + 1 < ne) {
-            const int r = C.elist[k + 1];
-            y1 = sqrtf(wts[r]) * C.G[(size_t)r * n + c];
-          }
-        }
-        lf *rec = stg + c * kStgRec;
-        if (bf) {
-          const float h0 = (float)(__bf16)y0, h1 = (float)(__bf16)y1;
-          reinterpret_cast<lu *>(rec)[kp] = bf16_pair(y0, y1);
-          reinterpret_cast<lu *>(rec)[8 + kp] = bf16_pair(y0 - h0, y1 - h1);
-        } else {
-          rec[2 * kp] = y0;
-          rec[2 * kp + 1] = y1;
         }
       }
+    };
+    auto stage = [&](int cb) {
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        const int kp = wid + W * i;
+        if (kp < 8) {
+#pragma unroll
+          for (int q = 0; q < kCols; ++q) {
+            const int c = cb + lane + 64 * q;
+            if (c < n16) {
+              const float y0 = y[i][q][0], y1 = y[i][q][1];
+              lf *rec = stg + c * kStgRec;
+              if (bf) {
+                const float h0 = (float)(__bf16)y0, h1 = (float)(__bf16)y1;
+                reinterpret_cast<lu *>(rec)[kp] = bf16_pair(y0, y1);
+                reinterpret_cast<lu *>(rec)[8 + kp] = bf16_pair(y0 - h0, y1 - h1);
+              } else {
+                rec[2 * kp] = y0;
+                rec[2 * kp + 1] = y1;
+              }
+            }
+          }
+        }
+      }
+    };
+    if (ne > 0) load(0, 0);
+    for (int k0 = 0; k0 < ne; k0 += 16) {
+      __syncthreads();  // the previous chunk has been consumed
+      stage(0);
+      for (int cb = 64 * kCols; cb < n16; cb += 64 * kCols) {
+        load(k0, cb);
+        stage(cb);
+      }
       __syncthreads();
+      if (k0 + 16 < ne) load(k0 + 16, 0);
 #pragma unroll
       for (int j = 0; j < kAsmTiles; ++j) {
         if (!val[j]) continue;
@@ -1733,7 +1956,17 @@ QPD void assemble_h_mfma(CT &C, int ne, const lf *wts) {
         }
       }
     }
-    // result layout: register r of lane l is row 4(l/16) + r, column l%16
+    // result layout: register r of lane l is row 4(l/16) + r, column l%16;
+    // all of Q's entries before the stores
+    f4v qv[kAsmTiles];
+#pragma unroll
+    for (int j = 0; j < kAsmTiles; ++j) {
+      if (!val[j]) continue;
+      const int col = 16 * tj[j] + c16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        qv[j][r] = C.Q[(unsigned)(min(16 * ti[j] + 4 * g + r, n - 1) * n + min(col, n - 1))];
+    }
 #pragma unroll
     for (int j = 0; j < kAsmTiles; ++j) {
       if (!val[j]) continue;
@@ -1741,7 +1974,8 @@ QPD void assemble_h_mfma(CT &C, int ne, const lf *wts) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 16 * ti[j] + 4 * g + r;
-        if (row < n && col <= row) M[moff(row) + col] = C.Q[(size_t)row * n + col] + acc[j][r];
+        if (row < n && col <= row)
+          M[mrow<typename CT::MT>(N, row).at(col)] = qv[j][r] + acc[j][r];
       }
     }
   }
@@ -1755,10 +1989,11 @@ template <int T, class CT>
 QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, float delta) {
   CT C = uctx(Cin_);
   nb = rfl(nb); ne = rfl(ne); wts = rflp(wts); bounded = rfl(bounded); delta = rflf(delta);
-  const int n = C.n, p = C.p, tid = tidx();
-  auto *M = C.M.get();
+  typedef typename CT::MT MT;
+  const int n = C.n, p = C.p, tid = tidx(), N = n + nb + p;
+  MT *M = C.M;
   if (C.amode != 0) {
-    assemble_h_mfma<T>(C, ne, wts);
+    assemble_h_mfma<T>(C, N, ne, wts);
   } else {
   // H block in 4x4 tiles.  Rows of G_I are staged through LDS in chunks
   // (coalesced cooperative loads), then each tile thread reads its 4 + 4
@@ -1768,26 +2003,25 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
   lf *stage = C.part;
   int cap = 2 * T;
   if constexpr (std::is_same<typename CT::MT, lf>::value) {
-    const int N = n + nb + p;
     const int room = moff(N) - moff(n);
-    if (room > cap) { stage = (lf *)C.M + moff(n); cap = room; }
+    if (room > cap) { stage = C.M + moff(n); cap = room; }
   }
   const int R = max(1, cap / ldg);
   const int nt = (n + 3) >> 2;
   const int ntiles = nt * (nt + 1) / 2;
   // tile threads are split into `groups` that take every groups-th staged
   // row; group 0 writes Q + its sum, the others add theirs in a fixed order
-  const int groups = ntiles <= T ? min(4, T / ntiles) : 1;
+  const int groups = 1 + (2 * ntiles <= T) + (3 * ntiles <= T) + (4 * ntiles <= T);
   for (int tb = 0; tb < ntiles; tb += T) {
-    const int t = tb + (tid % (groups > 1 ? ntiles : T));
-    const int g = groups > 1 ? tid / ntiles : 0;
+    // with more than one group, tb = 0: group g has threads g ntiles ..
+    const int g = groups > 1 ? (tid >= ntiles) + (tid >= 2 * ntiles) + (tid >= 3 * ntiles) +
+                                   (tid >= 4 * ntiles) : 0;
+    const int t = tb + tid - g * ntiles;
     const bool act = t < ntiles && g < groups;
     int i0 = 0, j0 = 0;
     if (act) {
-      int ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-      while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
-      while (ti * (ti + 1) / 2 > t) --ti;
-      const int tj = t - ti * (ti + 1) / 2;
+      int ti, tj;
+      tile_ij(t, ti, tj);
       i0 = 4 * ti;
       j0 = 4 * tj;
     }
@@ -1803,59 +2037,77 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
       const int kr = min(R, ne - k0);
       __syncthreads();  // the previous chunk has been consumed
       // 16 lanes per staged row (4 columns each, blocks of 64), T/16 rows at
-      // a time: the loads of four row batches first, then the stores
+      // a time: the loads of eight row batches first, then the stores; the
+      // rows' weights next to them, in row order
       for (int jb = 0; jb < ldg; jb += 64) {
-        for (int r0 = 0; r0 < kr; r0 += 4 * (T / 16)) {
-          float e[4][4];
+        for (int r0 = 0; r0 < kr; r0 += 8 * (T / 16)) {
+          float e[8][4];
+          int j[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int r = min(r0 + u * (T / 16) + (tid >> 4), kr - 1);
-            load_row4(C.G + (size_t)C.elist[k0 + r] * n, n, 1, n, 0, jb, tid & 15, e[u]);
+          for (int q = 0; q < 4; ++q) j[q] = min(jb + (tid & 15) + 16 * q, n - 1);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            if (r0 + u * (T / 16) < kr) {
+              const int r = C.elist[k0 + min(r0 + u * (T / 16) + (tid >> 4), kr - 1)];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) e[u][q] = C.G[(unsigned)(r * n + j[q])];
+            }
           }
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
+          for (int u = 0; u < 8; ++u) {
             const int r = r0 + u * (T / 16) + (tid >> 4);
             if (r < kr) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
-                const int j = jb + (tid & 15) + 16 * q;
-                if (j < ldg) stage[r * ldg + j] = e[u][q];
+                const int jq = jb + (tid & 15) + 16 * q;
+                if (jq < ldg) stage[r * ldg + jq] = jq < n ? e[u][q] : 0.f;
               }
             }
           }
         }
       }
+      for (int r = tid; r < kr; r += T) C.t0[r] = wts[C.elist[k0 + r]];
       __syncthreads();
       if (act) {
-#pragma unroll 2
-        for (int r = g; r < kr; r += groups) {
-          const float w = wts[C.elist[k0 + r]];
-          const f4v gi = *reinterpret_cast<const lf4 *>(stage + r * ldg + i0);
-          const f4v gj = *reinterpret_cast<const lf4 *>(stage + r * ldg + j0) * w;
-          const float gia[4] = {gi.x, gi.y, gi.z, gi.w};
-          const float gja[4] = {gj.x, gj.y, gj.z, gj.w};
+        const lf *si = stage + i0, *sj = stage + j0, *sw = C.t0;
+        // four rows' loads before their arithmetic
+        for (int r = g; r < kr; r += 4 * groups) {
+          f4v gi[4], gj[4];
+          float w[4];
 #pragma unroll
-          for (int a = 0; a < 4; ++a)
+          for (int u = 0; u < 4; ++u) {
+            const int ru = min(r + u * groups, kr - 1);
+            gi[u] = *reinterpret_cast<const lf4 *>(si + ru * ldg);
+            gj[u] = *reinterpret_cast<const lf4 *>(sj + ru * ldg);
+            w[u] = sw[ru];
+          }
 #pragma unroll
-            for (int bq = 0; bq < 4; ++bq) acc[a][bq] = fmaf(gia[a], gja[bq], acc[a][bq]);
+          for (int u = 0; u < 4; ++u) {
+            if (r + u * groups < kr) {
+              const f4v gw = gj[u] * w[u];
+#pragma unroll
+              for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int bq = 0; bq < 4; ++bq) acc[a][bq] = fmaf(gi[u][a], gw[bq], acc[a][bq]);
+            }
+          }
         }
       }
     }
+    // rows i0 .. i0+3 lie in one 16-row block, and every 4-column run of a
+    // row is a 16-byte one (right of the diagonal it is scratch)
+    typedef typename Vec4<MT>::type V4;
+    const int rs = std::is_same<MT, lf>::value ? 20 + (i0 & ~15) : kNB;
+    MT *Mt = M + mrow<MT>(N, i0).at(j0);
     for (int gg = 0; gg < groups; ++gg) {
       __syncthreads();  // staging area (may alias M's border rows) / previous group
       if (act && g == gg) {
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const int i = i0 + a;
-          if (i < n) {
-#pragma unroll
-            for (int bq = 0; bq < 4; ++bq) {
-              const int j = j0 + bq;
-              if (j <= i) {
-                if (gg == 0) M[moff(i) + j] = acc[a][bq];
-                else M[moff(i) + j] += acc[a][bq];
-              }
-            }
+          if (i0 + a < n) {
+            V4 *d = reinterpret_cast<V4 *>(Mt + a * rs);
+            const f4v v = {acc[a][0], acc[a][1], acc[a][2], acc[a][3]};
+            *d = gg == 0 ? v : *d + v;
           }
         }
       }
@@ -1866,51 +2118,80 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
   QPK_PT(PH_ASM);
   // border rows: [C | -Dl (lower part)].  C = [G_B; A] copied by 16 lanes
   // per row, which also take each row's squared norm for the border
-  // equilibration of the factorisation (border_exponent); then the lower
-  // triangle of the diagonal block.
+  // equilibration of the factorisation (border_exponent) and write its part
+  // of the lower triangle of the diagonal block.  Four row batches' loads go
+  // before their stores.
   const int K = nb + p;
   {
     constexpr int NG = T / 16;
     const int sub = tid & 15, grp = tid >> 4;
     float el = (float)kNoExp;
-    for (int k0 = 0; k0 < K; k0 += NG) {
+    for (int k0 = 0; k0 < K; k0 += 4 * NG) {
       // groups past the last row repeat it (the row reduction needs all 16
       // lanes) and store nothing
-      const int k = k0 + grp, kc = min(k, K - 1);
-      const gf *src = kc < nb ? C.G.get() + (size_t)C.bidx[kc] * n : C.A.get() + (size_t)(kc - nb) * n;
-      auto *row = M + moff(n + kc);
-      float ss = 0.f;
-      for (int j = sub; j < n; j += 16) {
-        const float v = src[j];
-        if (k < K) row[j] = v;
-        ss = fmaf(v, v, ss);
+      const gf *src[4];
+      float ss[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int kc = min(k0 + u * NG + grp, K - 1);
+        src[u] = kc < nb ? C.G + (size_t)C.bidx[kc] * n : C.A + (size_t)(kc - nb) * n;
+        ss[u] = 0.f;
       }
-      border_exponent(M, n + kc, k < K, sub, ss, el);
+      for (int jb = 0; jb < n; jb += 64) {
+        float e[4][4];
+        int jc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) jc[q] = min(jb + sub + 16 * q, n - 1);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (k0 + u * NG < K) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) e[u][q] = src[u][(unsigned)jc[q]];
+          }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + u * NG + grp;
+          const MRow<MT> row = mrow<MT>(N, n + min(k, K - 1));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int j = jb + sub + 16 * q;
+            if (k0 + u * NG < K && j < n) {
+              if (k < K) M[row.at(j)] = e[u][q];
+              ss[u] = fmaf(e[u][q], e[u][q], ss[u]);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u * NG + grp;
+        if (k0 + u * NG < K) {
+          border_exponent(C.dinv, n + min(k, K - 1), k < K, sub, ss[u], el);
+          if (k < K) {
+            const MRow<MT> row = mrow<MT>(N, n + k);
+            for (int l = sub; l < k; l += 16) M[row.at(n + l)] = 0.f;
+            if (sub == 0) {
+              float dl = 0.f;
+              if (k < nb && bounded) {
+                const int r = C.bidx[k];
+                dl = C.D[r] / C.E[r];
+              }
+              M[row.at(n + k)] = -(dl + delta);
+            }
+          }
+        }
+      }
     }
     border_exponents_done<T>(el, C.iflag);
   }
-  QPK_PT(PH_ASM_BORDER);
-  for (int e = tid; e < K * K; e += T) {
-    const int k = e / K, l = e - k * K;
-    if (l > k) continue;
-    float val = 0.f;
-    if (l == k) {
-      float dl = 0.f;
-      if (k < nb && bounded) {
-        const int r = C.bidx[k];
-        dl = C.D[r] / C.E[r];
-      }
-      val = -(dl + delta);
-    }
-    M[moff(n + k) + n + l] = val;
-  }
   __syncthreads();
+  QPK_PT(PH_ASM_BORDER);
 }
 
 // dinv[j] = 1 / L[j][j]
 template <int T, class CT>
 QPD void make_dinv(CT &C, int N) {
-  for (int j = tidx(); j < N; j += T) C.dinv[j] = 1.f / C.M[moff(j) + j];
+  for (int j = tidx(); j < N; j += T) C.dinv[j] = 1.f / C.M[mrow<typename CT::MT>(N, j).at(j)];
   __syncthreads();
 }
 
@@ -1919,7 +2200,7 @@ template <int T, int RPL, class CT>
 QPK_PHASE void solve2(CT &Cin_, int N, bool both) {
   CT C = uctx(Cin_);
   N = rfl(N); both = rfl(both);
-  signed_solve<T, RPL>(C.M.get(), N, C.n, C.dinv, C.u0, C.u1, both, C.mz.get(), C.part);
+  signed_solve<T, RPL>(C.M, N, C.n, C.dinv, C.u0, C.u1, both, C.mz, C.part);
   __syncthreads();
 }
 
@@ -1947,11 +2228,11 @@ template <int T, class AT, class CT>
 QPD void kkt_apply(CT &C, int nb, bool bounded, const lf *w, const lf *u, lf *out, bool sub) {
   typedef typename LdsT<AT>::type la;
   const int n = C.n, m = C.m, p = C.p, tid = tidx();
-  la *gx = reinterpret_cast<la *>(C.dd.get()), *ax = gx + m, *phi = gx + m + p, *kx = gx + 2 * m + p;
-  la *pd = reinterpret_cast<la *>(C.part.get());
+  la *gx = reinterpret_cast<la *>(C.dd), *ax = gx + m, *phi = gx + m + p, *kx = gx + 2 * m + p;
+  la *pd = reinterpret_cast<la *>(C.part);
   // G u, A u and Q'u_x + A'u_y in one pass; then G' phi, which needs G u
   float unused[3];
-  kkt_matvecs<T, AT>(C.Q, C.G, C.A, n, m, p, u, u, false, u + n + nb, gx, ax, kx, pd, unused[0],
+  kkt_matvecs<T, CT::U, AT>(C.Q, C.G, C.A, n, m, p, u, u, false, u + n + nb, gx, ax, kx, pd, unused[0],
                      unused[1], unused[2]);
   for (int i = tid; i < m; i += T) {
     const int k = C.role[i];
@@ -1959,7 +2240,7 @@ QPD void kkt_apply(CT &C, int nb, bool bounded, const lf *w, const lf *u, lf *ou
     phi[i] = k >= 0 ? (AT)u[n + k] : wi * gx[i];
   }
   __syncthreads();
-  if (m) coldot_d<T, AT>(C.G.get(), n, m, n, phi, kx, true, pd);
+  if (m) coldot_d<T, AT>(C.G, n, m, n, phi, kx, true, pd);
   const AT sg = sub ? (AT)-1 : (AT)1;
   for (int j = tid; j < n; j += T) out[j] = (float)((sub ? (AT)w[j] : (AT)0) + sg * kx[j]);
   for (int k = tid; k < nb; k += T) {
@@ -2026,7 +2307,7 @@ QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int s
     }
     if (it == steps) break;
     prev = nrm;
-    signed_solve<T, RPL>(C.M.get(), N, n, C.dinv, r, r, false, C.mz.get(), C.part);
+    signed_solve<T, RPL>(C.M, N, n, C.dinv, r, r, false, C.mz, C.part);
     __syncthreads();
     for (int j = tid; j < N; j += T) {
       C.rd[j] = r[j];
@@ -2079,20 +2360,21 @@ template <int T, class CT>
 QPK_PHASE void border_delta(CT &Cin_, int nb, float rel, float floor_abs) {
   CT C = uctx(Cin_);
   nb = rfl(nb); rel = rflf(rel); floor_abs = rflf(floor_abs);
-  const int n = C.n, K = nb + C.p, tid = tidx();
+  typedef typename CT::MT MT;
+  const int n = C.n, K = nb + C.p, N = n + K, tid = tidx();
   float mx[2] = {0.f, 0.f};
-  for (int j = tid; j < n; j += T) mx[0] = fmaxf(mx[0], C.M[moff(j) + j]);
+  for (int j = tid; j < n; j += T) mx[0] = fmaxf(mx[0], C.M[mrow<MT>(N, j).at(j)]);
   for (int k = tid; k < K; k += T) {
     float ss = 0.f;
     for (int j = 0; j < n; ++j) {
-      const float c = C.M[moff(n + k) + j];
+      const float c = C.M[mrow<MT>(N, n + k).at(j)];
       ss = fmaf(c, c, ss);
     }
     mx[1] = fmaxf(mx[1], ss);
   }
   block_reduce<T, OpMax, 2>(mx, C.red);
   const float delta = fmaxf(fmaxf(rel * mx[1] / fmaxf(mx[0], 1e-30f), floor_abs), 1e-30f);
-  for (int k = tid; k < K; k += T) C.M[moff(n + k) + n + k] -= delta;
+  for (int k = tid; k < K; k += T) C.M[mrow<MT>(N, n + k).at(n + k)] -= delta;
   __syncthreads();
 }
 
@@ -2125,7 +2407,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     border_delta<T>(C, nb, delta_rel, 0.f);
   }
   QPK_PT(PH_ASM_DIAG);
-  bool ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, C.dyn != 0, C.part);
+  bool ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, C.dyn != 0, C.part, C.dinv);
   QPK_PT(PH_FACT);
   *regularised = delta_rel > 0.f || floor || C.iflag[2] > 0;
   if (!ok && C.dyn) {
@@ -2134,7 +2416,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     const float pmax = __int_as_float(C.iflag[4]);
     assemble<T>(C, nb, ne, wts, true, 0.f);
     border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * pmax);
-    ok = signed_cholesky<T, RPL>(C.M.get(), N, C.n, C.iflag, true, C.part);
+    ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, true, C.part, C.dinv);
     *regularised = true;
   }
   return ok;
@@ -2182,11 +2464,11 @@ QPK_PHASE void rhs_bounded(CT &Cin_, int nb, float kappa, const gf *gx, const gf
     if (!adj) {
       const lf *xv[2] = {C.t0, C.t1};
       lf *o[2] = {C.tGz, C.tAy};
-      coldot<T, 2>(C.G.get(), n, m, n, xv, o, C.part);
+      coldot<T, CT::U, 2>(C.G, n, m, n, xv, o, C.part);
     } else {
       const lf *xv[1] = {C.t0};
       lf *o[1] = {C.tGz};
-      coldot<T, 1>(C.G.get(), n, m, n, xv, o, C.part);
+      coldot<T, CT::U, 1>(C.G, n, m, n, xv, o, C.part);
     }
   }
   for (int i = tid; i < n; i += T) {
@@ -2221,11 +2503,11 @@ QPK_PHASE void recover_bounded(CT &Cin_, int nb, bool both) {
   if (both) {
     const lf *xv[2] = {C.u0, C.u1};
     lf *o[2] = {C.t0, C.t1};
-    rowdot<T, 2>(C.G.get(), n, m, n, xv, o);
+    rowdot<T, CT::U, 2>(C.G, n, m, n, xv, o);
   } else {
     const lf *xv[1] = {C.u0};
     lf *o[1] = {C.t0};
-    rowdot<T, 1>(C.G.get(), n, m, n, xv, o);
+    rowdot<T, CT::U, 1>(C.G, n, m, n, xv, o);
   }
   __syncthreads();
   for (int i = tid; i < m; i += T) {
@@ -2275,12 +2557,12 @@ QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
   const int ne = compact_rows<T>(C.role, m, C.elist, C.red);
   assemble<T>(C, 0, ne, C.E, false, 0.f);
   const int N = n + p;
-  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, dyn, C.part);
+  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, dyn, C.part, C.dinv);
   make_dinv<T>(C, N);
   if (m) {
     const lf *hv[1] = {C.h};
     lf *o[1] = {C.tGz};
-    coldot<T, 1>(C.G.get(), n, m, n, hv, o, C.part);
+    coldot<T, CT::U, 1>(C.G, n, m, n, hv, o, C.part);
   }
   for (int i = tid; i < n; i += T) C.u0[i] = C.w0[i] = -C.q[i] + (m ? C.tGz[i] : 0.f);
   for (int k = tid; k < p; k += T) C.u0[n + k] = C.w0[n + k] = C.b[k];
@@ -2296,7 +2578,7 @@ QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
   if (m) {
     const lf *xv[1] = {C.x};
     lf *o[1] = {C.t0};
-    rowdot<T, 1>(C.G.get(), n, m, n, xv, o);
+    rowdot<T, CT::U, 1>(C.G, n, m, n, xv, o);
     __syncthreads();
     float mx[2] = {-kBig, -kBig};
     for (int i = tid; i < m; i += T) {
@@ -2477,7 +2759,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
   __syncthreads();
   const int N = n + p;
   assemble<T>(C, 0, ne, C.E, false, delta_reg);
-  const bool ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false, C.part);
+  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.dinv);
   const double dn = n, dm = m, dp = p, dN = N;
   work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;
   work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0;
@@ -2492,7 +2774,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
     {
       const lf *xv[1] = {C.t0};
       lf *o[1] = {C.tGz};
-      if (m) coldot<T, 1>(C.G.get(), n, m, n, xv, o, C.part);
+      if (m) coldot<T, CT::U, 1>(C.G, n, m, n, xv, o, C.part);
     }
     for (int i = tid; i < n; i += T) C.u0[i] = -C.rt[i] - (m ? C.tGz[i] : 0.f);
     for (int k = tid; k < p; k += T) C.u0[n + k] = -C.re[k];
@@ -2500,7 +2782,7 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
     solve2<T, RPL>(C, N, false);
     const lf *xv[1] = {C.u0};
     lf *o[1] = {C.t0};
-    if (m) rowdot<T, 1>(C.G.get(), n, m, n, xv, o);
+    if (m) rowdot<T, CT::U, 1>(C.G, n, m, n, xv, o);
     __syncthreads();
   };
   float sgm;
@@ -2595,13 +2877,14 @@ QPD float direct_backward_error(CT &C) {
 // Newton loop shared by the solve, the relaxation and the serving step.
 // Returns the final status; iters counts Newton steps taken.
 template <int T, int RPL, class CT>
-QPD int newton_loop(CT &C, bool bounded, int max_iter, float tol, int kt_mode, float sigma,
+QPD int newton_loop(CT &Cin_, bool bounded, int max_iter, float tol, int kt_mode, float sigma,
                     float kr, float delta_reg, int refine_steps, double &work, int &iters,
                     float &res) {
-  const int m = C.m, tid = tidx();
   int status = ST_MAXIT;
   int stage = SG_NONE;
   for (int it = 0;; ++it) {
+    CT C = uctx(Cin_);
+    const int m = C.m, tid = tidx();
     // manifold coordinates v = z - s, kappa = s'z / m
     float sm[1] = {0.f};
     for (int i = tid; i < m; i += T) {
@@ -2758,7 +3041,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     for (int i = tid; i < m; i += T) C.dv0[i] = C.E[i] * (C.dv0[i] + (gz ? gz[i] : 0.f));
   } else {
     assemble<T>(C, nb, ne, C.t1, false, 0.f);
-    ok = signed_cholesky<T, RPL>(C.M.get(), N, n, C.iflag, false, C.part);
+    ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.dinv);
     const int nref = plain_refine_steps(C.rmode, refine_steps, 2);
     work += wfac + nref * wstep;
     if (!ok) return kAdjFactorFail;
@@ -2769,7 +3052,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     if (m) {
       const lf *xv[1] = {C.t0};
       lf *o[1] = {C.tGz};
-      coldot<T, 1>(C.G.get(), n, m, n, xv, o, C.part);
+      coldot<T, CT::U, 1>(C.G, n, m, n, xv, o, C.part);
     }
     for (int i = tid; i < n; i += T) C.u0[i] = C.w0[i] = -gx[i] - (m ? C.tGz[i] : 0.f);
     for (int k = tid; k < p; k += T) C.u0[n + k] = C.w0[n + k] = gy ? -gy[k] : 0.f;
@@ -2783,7 +3066,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     if (m) {
       const lf *xv[1] = {C.u0};
       lf *o[1] = {C.t0};
-      rowdot<T, 1>(C.G.get(), n, m, n, xv, o);
+      rowdot<T, CT::U, 1>(C.G, n, m, n, xv, o);
     }
     __syncthreads();
     for (int i = tid; i < m; i += T) C.dv0[i] = C.E[i] * (C.t0[i] + (gz ? gz[i] : 0.f));
@@ -2854,7 +3137,6 @@ QPK_PHASE void write_grads(CT &Cin_, const Params &P, size_t qi) {
 // ---------------------------------------------------------------------------
 template <int T, int RPL, bool MLDS, int MODE>
 QPD void qp_body(const Params &P) {
-  extern __shared__ __attribute__((aligned(16))) float smem[];
   typedef typename std::conditional<MLDS, lf, gf>::type MF;
   const size_t qi = blockIdx.x;
   // sizes and data pointers: from the batch (solve / backward) or from this
@@ -2877,15 +3159,13 @@ QPD void qp_body(const Params &P) {
     hp = m ? P.h + qi * (size_t)m : nullptr;
     wsp = MLDS ? nullptr : P.ws + (size_t)qi * P.ws_stride;
   }
-  const Layout L = make_layout(n, m, p, kb, MLDS, T);
-  lf *sm = (lf *)smem;
-  MF *Mp;
-  if constexpr (MLDS) Mp = sm + L.M;
-  else Mp = (gf *)wsp;
-  Ctx<MF> C;
-  init_ctx(C, sm, L, Mp, (const gf *)Qp, (const gf *)qp, (const gf *)Ap, (const gf *)bp,
-           (const gf *)Gp, (const gf *)hp);
-  __syncthreads();  // the context table
+  Ctx<T, RPL, MF> C;
+  C.n = n; C.m = m; C.p = p; C.kb = kb;
+  C.Q = (const gf *)Qp; C.q_g = (const gf *)qp; C.A = (const gf *)Ap;
+  C.b_g = (const gf *)bp; C.G = (const gf *)Gp; C.h_g = (const gf *)hp;
+  if constexpr (MLDS) C.Mg = nullptr;
+  else C.Mg = (gf *)wsp;
+  place(C);
   if constexpr (MODE == kServe) C.amode = (P.desc[qi].flags >> 1) & 3;
   else C.amode = P.asm_mode;
   const int amode0 = C.amode;
@@ -2910,6 +3190,7 @@ QPD void qp_body(const Params &P) {
 #endif
   load_vectors<T>(C);
   double work = 0.0;
+  const Ctx<T, RPL, MF> C0 = C;
   int iters = 0;
   float res = 0.f;
   int status;
@@ -2945,6 +3226,7 @@ QPD void qp_body(const Params &P) {
       status = newton_loop<T, RPL>(C, bounded, d.budget, P.tol, P.pc ? 0 : 1, P.sigma, 0.f,
                                    P.delta_reg, refine, work, iters, res);
     }
+    C = uctx(C0);
     for (int i = tid; i < n; i += T) st[i] = C.x[i];
     for (int k = tid; k < p; k += T) st[n + k] = C.y[k];
     for (int i = tid; i < m; i += T) {
@@ -2975,6 +3257,7 @@ QPD void qp_body(const Params &P) {
       status = newton_loop<T, RPL>(C, bounded, P.max_iter, P.tol, P.pc ? 0 : 1, P.sigma, 0.f,
                                    P.delta_reg, refine, work, iters, res);
     }
+    C = uctx(C0);
     gf *xo = (gf *)P.x + qi * (size_t)n;
     for (int i = tid; i < n; i += T) xo[i] = C.x[i];
     if (p && P.y) for (int k = tid; k < p; k += T) ((gf *)P.y)[qi * p + k] = C.y[k];
@@ -3025,6 +3308,7 @@ QPD void qp_body(const Params &P) {
     if (adj == kAdjFactorFail) status = mkstatus(ST_FACT, SG_RELAX);
     else if (adj == kAdjInaccurate && (status & 0xff) == ST_CONV) status = mkstatus(ST_MAXIT, SG_BWD);
     __syncthreads();
+    C = uctx(C0);
     write_grads<T>(C, P, qi);
     if (P.rx) for (int i = tid; i < n; i += T) ((gf *)P.rx)[qi * n + i] = C.x[i];
     if (P.ry && p) for (int k = tid; k < p; k += T) ((gf *)P.ry)[qi * p + k] = C.y[k];
