@@ -146,7 +146,7 @@ QPD void wave_sync() {
 // otherwise.
 enum Phase { PH_INIT, PH_RESID, PH_PART, PH_ASM, PH_FACT, PH_RHS, PH_SOLVE, PH_REFINE,
              PH_RECOVER, PH_STEP, PH_BWD, PH_OUT, PH_ASM_BORDER, PH_ASM_DIAG, PH_FACT_UPDATE,
-             PH_FACT_ELIM, PH_DINV, PH_MATVEC, PH_KAPPA, PH_AFFINE, PH_REFINE_APPLY, PH_N = 32 };
+             PH_FACT_ELIM, PH_MATVEC, PH_KAPPA, PH_AFFINE, PH_REFINE_APPLY, PH_N = 32 };
 #ifdef QPK_PHASE_TIMING
 static __shared__ long long qpk_pt[PH_N];  // the last entry: the previous mark's clock
 #define QPK_PT(k)                                       \
@@ -262,14 +262,22 @@ QPD void block_reduce(float (&v)[K], lf *red) {
 }
 
 // ---------------------------------------------------------------------------
-// Softplus retraction, cancellation-free (appendix C).
-QPD float bk(float v, float kappa) {
-  const float r = sqrtf(fmaf(v, v, 4.f * kappa));
-  return v >= 0.f ? 0.5f * (v + r) : 2.f * kappa / (r - v);
+// Softplus retraction, cancellation-free (appendix C): b_kappa(v) =
+// (v + r)/2 for v >= 0, 2 kappa / (r - v) for v < 0, r = sqrt(v^2 + 4 kappa).
+// Both signs of v at once: one root and one division.
+QPD void bk2(float v, float kappa, float &bp, float &bm) {  // b(v), b(-v)
+  const float av = fabsf(v), r = sqrtf(fmaf(v, v, 4.f * kappa));
+  const float big = 0.5f * (av + r), small = 2.f * kappa / (r + av);
+  bp = v >= 0.f ? big : small;
+  bm = v <= 0.f ? big : small;
 }
-// b_kappa'(v): (1 + v/r)/2 for v >= 0, 2 kappa / (r^2 - v r) for v < 0.
-QPD float dbk(float v, float kappa, float r) {
-  return v >= 0.f ? 0.5f * (1.f + v / r) : 2.f * kappa / (r * (r - v));
+// b_kappa'(v): (1 + v/r)/2 for v >= 0, 2 kappa / (r^2 - v r) for v < 0; again
+// for both signs, with one division each.
+QPD void dbk2(float v, float kappa, float r, float &dp, float &dm) {  // b'(v), b'(-v)
+  const float av = fabsf(v);
+  const float big = 0.5f * (1.f + av / r), small = 2.f * kappa / (r * (r + av));
+  dp = v >= 0.f ? big : small;
+  dm = v <= 0.f ? big : small;
 }
 
 // ---------------------------------------------------------------------------
@@ -332,13 +340,13 @@ struct Layout {
   int part, red;                        // partial sums, reduction scratch
   int u0, u1, rr, rd;                   // right-hand sides; residual and last
                                         // correction of the refinement
-  int dv0, dv1, dd, dinv;               // dd: FP64 scratch
+  int dv0, dv1, dd, ex;                 // dd: FP64 scratch; ex: border exponents
   int z, s, v, h, E, D, c, ri, rz, rs;
   int role, bidx, elist;
   int t0, t1;                           // also rhs copies of the refinement
   int x, q, rt, tGz, tAy;
   int y, b, re;
-  int stg, stg_len;  // assembly staging: the span part .. end of dinv, which
+  int stg, stg_len;  // assembly staging: the span part .. end of ex, which
                      // holds nothing live while the matrix is assembled
   int M;      // offset of M if in LDS, else -1
   int total;  // floats
@@ -359,8 +367,8 @@ __host__ __device__ inline Layout make_layout(int n, int m, int p, int kb, bool 
   L.u0 = b0; L.u1 = b0 + sN; L.rr = b0 + 2 * sN; L.rd = b0 + 3 * sN;
   L.dv0 = b0 + 4 * sN; L.dv1 = L.dv0 + sm;
   L.dd = L.dv0 + 2 * sm;
-  L.dinv = L.dd + al4(2 * (2 * m + p + n + 8));
-  const int b1 = L.dinv + ((L.Nmax + 15) & ~15);
+  L.ex = L.dd + al4(2 * (2 * m + p + n + 8));
+  const int b1 = L.ex + ((L.Nmax + 15) & ~15);
   L.stg = L.part;
   L.stg_len = b1 - L.part;
   L.z = b1; L.s = b1 + sm; L.v = b1 + 2 * sm; L.h = b1 + 3 * sm; L.E = b1 + 4 * sm;
@@ -790,8 +798,7 @@ QPD void store_row(MF *M, int i, int k0, const float (&P)[kNB]) {
 // is bit for bit the factor of the unscaled matrix wherever the scaled
 // tests decide as the unscaled ones would, and the factor with the scaled
 // tests' replacements otherwise.  The assembly computes e_i while it copies
-// the border rows and keeps it in ex[i] (the place of 1 / L[i][i], which is
-// computed after the factorisation), the per-wave maxima of e in flag[8 ..] (at most 8 waves).
+// the border rows and keeps it in ex[i], the per-wave maxima of e in flag[8 ..] (at most 8 waves).
 constexpr int kNoExp = -1000;
 template <int T>
 QPD int border_emax(const li *flag) {
@@ -1058,13 +1065,13 @@ QPD void load_run(const MF *p, bool in, float (&o)[RPL]) {
 }
 
 // Solve (L diag(sg) L') u = r in place for the right-hand side r (length N)
-// on WG waves (this one is wave g of them), the vector in registers; dinv[j]
-// = 1 / L[j][j].  The forward sweep walks rows of L, the backward sweep reads
+// on WG waves (this one is wave g of them), the vector and the pivots' inverses
+// in registers.  The forward sweep walks rows of L, the backward sweep reads
 // L[j][i] from row j.  16-row blocks are dealt to the waves in turn (block b
 // to wave b mod WG), S rows per lane (lane l owns local rows S l .. S l + S-1,
 // all in one block), so that a block's rows sit in fixed slots of 16 / S lanes.
 // For each 16-column block the owner runs its 16 dependent steps (scale the
-// row's value by its dinv, broadcast it, subtract it from every row) in
+// row's value by its pivot's inverse, broadcast it, subtract it from every row) in
 // registers; with more than one wave it then passes the 16 values on through
 // `ex` (two buffers of 16, taken in turn, so that one workgroup barrier per
 // block separates writer and readers), and the other waves subtract them from
@@ -1074,10 +1081,10 @@ QPD void load_run(const MF *p, bool in, float (&o)[RPL]) {
 // the diagonal inside every row's padded 16-column segment; rows that must
 // not be touched in a block read the zero row `zrow` (16 zeros stored after
 // M's last row, so both pointers are in M's address space), and rows past N-1
-// hold 0 with a dinv of 0, so the steps carry no tests.
+// hold 0 with an inverse of 0, so the steps carry no tests.
 template <int S, int WG, class MF>
-QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r, const MF *zrow,
-                            int g, lf *ex) {
+QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow, int g,
+                            lf *ex, li *bad) {
   typedef typename Vec4<const MF>::type CV4;
   static_assert(kNB % S == 0, "row slot must be static within a block");
   // columns in flight: two buffers of S x CW floats per lane
@@ -1091,8 +1098,8 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r,
   for (int t = 0; t < S; ++t) {
     const bool in = i0 + t < N;
     a[t] = in ? r[min(i0 + t, N - 1)] : 0.f;
-    dl[t] = in ? dinv[min(i0 + t, N - 1)] : 0.f;
     row[t] = M + moff(min(i0 + t, N - 1));
+    dl[t] = in ? 1.f / row[t][min(i0 + t, N - 1)] : 0.f;
   }
   const int nblk = (N + 15) >> 4;
   float nx[S][CW], Lc[S][CW];
@@ -1225,9 +1232,13 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r,
       }
     }
   }
+  bool nf = false;
 #pragma unroll
-  for (int t = 0; t < S; ++t)
+  for (int t = 0; t < S; ++t) {
     if (i0 + t < N) r[i0 + t] = a[t];
+    nf |= i0 + t < N && !finitef(a[t]);
+  }
+  if (nf) *bad = 1;
 }
 
 // The same solve, of one or two right-hand sides, with a factor in global
@@ -1243,8 +1254,8 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, const lf *dinv, lf *r,
 // cycles per block on the 64 cache lines of every load (n = 256); this takes
 // about 1K.
 template <int T, int RPL>
-QPD void signed_solve_tiles(const gf *M, int N, int npos, const lf *dinv, lf *r0, lf *r1,
-                            bool both, lf *ex) {
+QPD void signed_solve_tiles(const gf *M, int N, int npos, lf *r0, lf *r1, bool both,
+                            lf *ex, li *bad) {
   constexpr int NW = T / 64, S = RPL > NW ? RPL / NW : 1;
   const int lane = tidx() & 63, g = rfl(tidx() >> 6), c16 = lane & 15, sl = lane >> 4;
   const int nblk = (N + 15) >> 4, last = nblk - 1;
@@ -1257,7 +1268,7 @@ QPD void signed_solve_tiles(const gf *M, int N, int npos, const lf *dinv, lf *r0
     const bool in = i < N;
     a[0][t] = in ? r0[min(i, N - 1)] : 0.f;
     a[1][t] = in && both ? r1[min(i, N - 1)] : 0.f;
-    dl[t] = in ? dinv[min(i, N - 1)] : 0.f;
+    dl[t] = in ? 1.f / M[(unsigned)mrow<gf>(N, min(i, N - 1)).at(min(i, N - 1))] : 0.f;
   }
   f4v nt[S][4];
   // this lane's place in a tile (rows of the last tile row that do not exist
@@ -1381,33 +1392,36 @@ QPD void signed_solve_tiles(const gf *M, int N, int npos, const lf *dinv, lf *r0
     load_b(max(b - 1, 0));
     step(b, std::false_type{});
   }
+  bool nf = false;
 #pragma unroll
   for (int t = 0; t < S; ++t) {
     const int i = kNB * qi[t] + c16;
     if (i < N) {
       r0[i] = a[0][t];
       if (both) r1[i] = a[1][t];
+      nf |= !finitef(a[0][t]) || !finitef(a[1][t]);
     }
   }
+  if (nf) *bad = 1;
 }
 
 // The solves of one or two right-hand sides side by side.  With the factor in
 // LDS, up to 4 rows per lane one wave each (the chain of dependent steps
 // bounds them), above that half of the workgroup's waves each.  A barrier must
-// follow.
+// follow.  *bad is set if a solution has a non-finite entry.
 template <int T, int RPL, class MF>
-QPD void signed_solve(const MF *M, int N, int npos, const lf *dinv, lf *r0, lf *r1, bool both,
-                      const MF *zrow, lf *ex) {
+QPD void signed_solve(const MF *M, int N, int npos, lf *r0, lf *r1, bool both, const MF *zrow,
+                      lf *ex, li *bad) {
   if constexpr (std::is_same<MF, lf>::value) {
     constexpr int WG = RPL > 4 ? T / 128 : 1, S = RPL / WG;
     const int wid = rfl(tidx() >> 6), k = wid / WG;
     if (k == 0 || (k == 1 && both)) {
-      signed_solve_waves<S, WG>(M, N, npos, dinv, k ? r1 : r0, zrow, wid % WG, ex + 32 * k);
+      signed_solve_waves<S, WG>(M, N, npos, k ? r1 : r0, zrow, wid % WG, ex + 32 * k, bad);
     } else if constexpr (WG > 1) {
       for (int b = 2 * ((N + 15) >> 4); b > 0; --b) __syncthreads();
     }
   } else {
-    signed_solve_tiles<T, RPL>(M, N, npos, dinv, r0, r1, both, ex);
+    signed_solve_tiles<T, RPL>(M, N, npos, r0, r1, both, ex, bad);
   }
 }
 
@@ -1548,17 +1562,18 @@ struct Ctx {
   MF *M;   // factor storage (LDS or global)
   lf *x, *y, *z, *s, *v, *q, *h, *b, *E, *D, *c;
   lf *rt, *ri, *re, *rz, *rs, *tGz, *tAy;
-  lf *t0, *t1, *u0, *u1, *dv0, *dv1, *dinv, *part, *red;
+  lf *t0, *t1, *u0, *u1, *dv0, *dv1, *ex, *part, *red;
   lf *w0, *w1, *rr, *rd;  // w0, w1: rhs copies of the refinement (in t0, t1)
   MF *mz;  // 16 zeros after M's last row (same address space as M)
   ldd *dd;
   li *role, *bidx, *elist, *iflag;
-  lf *stg;  // matrix-core assembly staging (aliases part .. dinv)
+  lf *stg;  // matrix-core assembly staging (aliases part .. ex)
   int amode;  // H-block assembly: 0 FP32 VALU, 1 BF16x3 MFMA, 2 FP32 MFMA
   int dyn;    // bounded form: regularise degenerate factorisations (R13)
   int rmode;  // residual precision: 0 FP32 first (FP64 refinement after a
               // stall), 1 FP64 residuals everywhere, 2 FP32 only
   float bo;   // line-search back-off factor (1 = none)
+  int wk;     // count algorithmic flops (FP64 arithmetic; only when asked for)
 };
 
 extern __shared__ __attribute__((aligned(16))) float qpk_smem[];
@@ -1574,7 +1589,7 @@ QPD void place(CT &C) {
   C.c = sm + L.c; C.rt = sm + L.rt; C.ri = sm + L.ri; C.re = sm + L.re; C.rz = sm + L.rz;
   C.rs = sm + L.rs; C.tGz = sm + L.tGz; C.tAy = sm + L.tAy; C.t0 = sm + L.t0; C.t1 = sm + L.t1;
   C.u0 = sm + L.u0; C.u1 = sm + L.u1; C.dv0 = sm + L.dv0; C.dv1 = sm + L.dv1;
-  C.dinv = sm + L.dinv; C.part = sm + L.part; C.red = sm + L.red;
+  C.ex = sm + L.ex; C.part = sm + L.part; C.red = sm + L.red;
   C.w0 = C.t0; C.w1 = C.t1; C.rr = sm + L.rr; C.rd = sm + L.rd;
   C.dd = reinterpret_cast<ldd *>(sm + L.dd);
   C.role = reinterpret_cast<li *>(sm + L.role);
@@ -1595,6 +1610,7 @@ QPD CT uctx(const CT &I) {
   C.Q = rflp(I.Q); C.q_g = rflp(I.q_g); C.A = rflp(I.A); C.b_g = rflp(I.b_g);
   C.G = rflp(I.G); C.h_g = rflp(I.h_g); C.Mg = rflp(I.Mg);
   C.amode = rfl(I.amode); C.dyn = rfl(I.dyn); C.rmode = rfl(I.rmode); C.bo = rflf(I.bo);
+  C.wk = rfl(I.wk);
   place(C);
   return C;
 }
@@ -1618,19 +1634,22 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
   // are produced
   la *gxd = reinterpret_cast<la *>(C.dd), *axd = gxd + m, *rtd = gxd + m + p;
   la *pd = reinterpret_cast<la *>(C.part);
-  enum { RT, QX, QQ, GZ, AY, RI, GX, SS, HH, RE, AX, BB, RZS, ZZ, CC, NF, NK };
+  // largest residuals and the scales they are measured against
+  enum { RT, RTS, RI, RIS, RE, RES, RZS, RZSS, CC, NF, NK };
   float mx[NK];
 #pragma unroll
   for (int k = 0; k < NK; ++k) mx[k] = 0.f;
-  kkt_matvecs<T, CT::U, AT>(C.Q, C.G, C.A, n, m, p, C.x, C.z, true, C.y, gxd, axd, rtd, pd, mx[QX],
-                     mx[GZ], mx[AY]);
+  float mq, mg, ma;
+  kkt_matvecs<T, CT::U, AT>(C.Q, C.G, C.A, n, m, p, C.x, C.z, true, C.y, gxd, axd, rtd, pd, mq, mg,
+                            ma);
+  mx[RTS] = fmaxf(mq, fmaxf(mg, ma));
   QPK_PT(PH_MATVEC);
   const bool man = bounded && kr > 0.f;  // relaxation of an implicit form
   for (int i = tid; i < n; i += T) {
     const float r = (float)(rtd[i] + (AT)C.q[i]);
     C.rt[i] = r;
     mx[RT] = fmaxf(mx[RT], fabsf(r));
-    mx[QQ] = fmaxf(mx[QQ], fabsf(C.q[i]));
+    mx[RTS] = fmaxf(mx[RTS], fabsf(C.q[i]));
     if (!finitef(r)) mx[NF] = 1.f;
   }
   for (int i = tid; i < m; i += T) {
@@ -1639,15 +1658,15 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
     const float r = (float)(gx + (AT)si - (AT)C.h[i]);
     C.ri[i] = r;
     mx[RI] = fmaxf(mx[RI], fabsf(r));
-    mx[GX] = fmaxf(mx[GX], fabsf((float)gx));
-    mx[SS] = fmaxf(mx[SS], fabsf(si));
-    mx[HH] = fmaxf(mx[HH], fabsf(C.h[i]));
-    mx[ZZ] = fmaxf(mx[ZZ], fabsf(zi));
+    mx[RIS] = fmaxf(fmaxf(mx[RIS], fabsf((float)gx)), fmaxf(fabsf(si), fabsf(C.h[i])));
+    mx[RZSS] = fmaxf(mx[RZSS], fmaxf(fabsf(zi), fabsf(si)));
     float rz = 0.f, rs = 0.f;
     if (bounded) {
       const float vi = C.v[i];
-      rz = zi - bk(vi, kappa);
-      rs = si - bk(-vi, kappa);
+      float bz, bs;
+      bk2(vi, kappa, bz, bs);
+      rz = zi - bz;
+      rs = si - bs;
       C.rz[i] = rz;
       C.rs[i] = rs;
     }
@@ -1661,15 +1680,14 @@ QPK_PHASE float residuals(CT &Cin_, bool bounded, float kappa, float kr, bool *b
     const float r = (float)(ax - (AT)C.b[i]);
     C.re[i] = r;
     mx[RE] = fmaxf(mx[RE], fabsf(r));
-    mx[AX] = fmaxf(mx[AX], fabsf((float)ax));
-    mx[BB] = fmaxf(mx[BB], fabsf(C.b[i]));
+    mx[RES] = fmaxf(mx[RES], fmaxf(fabsf((float)ax), fabsf(C.b[i])));
     if (!finitef(r)) mx[NF] = 1.f;
   }
   block_reduce<T, OpMax, NK>(mx, C.red);
-  const float rt_s = mx[RT] / (1.f + fmaxf(fmaxf(mx[QX], mx[QQ]), fmaxf(mx[GZ], mx[AY])));
-  const float ri_s = m ? mx[RI] / (1.f + fmaxf(mx[GX], fmaxf(mx[SS], mx[HH]))) : 0.f;
-  const float re_s = p ? mx[RE] / (1.f + fmaxf(mx[AX], mx[BB])) : 0.f;
-  const float rzs = m ? mx[RZS] / (1.f + fmaxf(mx[ZZ], mx[SS])) : 0.f;
+  const float rt_s = mx[RT] / (1.f + mx[RTS]);
+  const float ri_s = m ? mx[RI] / (1.f + mx[RIS]) : 0.f;
+  const float re_s = p ? mx[RE] / (1.f + mx[RES]) : 0.f;
+  const float rzs = m ? mx[RZS] / (1.f + mx[RZSS]) : 0.f;
   const float cc = m ? (man ? fabsf(kappa - kr) / kr : mx[CC]) : 0.f;
   *bad = mx[NF] != 0.f;
   return fmaxf(fmaxf(rt_s, ri_s), fmaxf(fmaxf(re_s, rzs), cc));
@@ -1715,84 +1733,84 @@ QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
   constexpr int NW = T / 64;
   li *ws = reinterpret_cast<li *>(C.red);  // per-wave counts [2][NW]
   const unsigned long long below = (1ull << lane) - 1ull;
-  // One sweep: retraction derivatives, and the border / eliminated lists in
-  // row order from wave ballots (the common case: at most kb rows with v > 0)
+  // The border / eliminated lists in row order, from wave ballots: row i goes
+  // to the border if bord(i)
   int nb = 0, ne = 0;
-  for (int i0 = 0; i0 < m; i0 += T) {
-    const int i = i0 + tid;
-    const bool valid = i < m;
-    bool f = false;
-    if (valid) {
-      const float vi = C.v[i];
-      const float r = sqrtf(fmaf(vi, vi, 4.f * kappa));
-      C.E[i] = dbk(vi, kappa, r);
-      C.D[i] = dbk(-vi, kappa, r);
-      C.c[i] = 1.f / r;
-      f = vi > 0.f;
-    }
-    const unsigned long long bb = __ballot(valid && f), be = __ballot(valid && !f);
-    if (lane == 0) {
-      ws[w] = __popcll(bb);
-      ws[NW + w] = __popcll(be);
-    }
-    __syncthreads();
-    int ob = 0, oe = 0, tb = 0, te = 0;
-#pragma unroll
-    for (int k = 0; k < NW; ++k) {
-      const int cb = ws[k], ce = ws[NW + k];
-      ob += k < w ? cb : 0;
-      oe += k < w ? ce : 0;
-      tb += cb;
-      te += ce;
-    }
-    if (valid) {
-      if (f) {
-        const int k = nb + ob + __popcll(bb & below);
-        if (k < kb) C.bidx[k] = i;
-        C.role[i] = k;
-      } else {
-        C.elist[ne + oe + __popcll(be & below)] = i;
-        C.role[i] = -1;
+  auto lists = [&](auto bord) {
+    nb = ne = 0;
+    for (int i0 = 0; i0 < m; i0 += T) {
+      const int i = i0 + tid;
+      const bool valid = i < m;
+      const bool f = valid && bord(i);
+      const unsigned long long bb = __ballot(f), be = __ballot(valid && !f);
+      if (lane == 0) {
+        ws[w] = __popcll(bb);
+        ws[NW + w] = __popcll(be);
       }
+      __syncthreads();
+      int ob = 0, oe = 0, tb = 0, te = 0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        const int cb = ws[k], ce = ws[NW + k];
+        ob += k < w ? cb : 0;
+        oe += k < w ? ce : 0;
+        tb += cb;
+        te += ce;
+      }
+      if (valid) {
+        if (f) {
+          const int k = nb + ob + __popcll(bb & below);
+          if (k < kb) C.bidx[k] = i;
+          C.role[i] = k;
+          C.t0[k] = C.v[i];  // the candidates' v, in row order
+        } else {
+          C.elist[ne + oe + __popcll(be & below)] = i;
+          C.role[i] = -1;
+        }
+      }
+      nb += tb;
+      ne += te;
+      __syncthreads();
     }
-    nb += tb;
-    ne += te;
-    __syncthreads();
-  }
+  };
+  // the common case, at most kb rows with v > 0: one sweep with the
+  // retraction derivatives
+  lists([&](int i) {
+    const float vi = C.v[i];
+    const float r = sqrtf(fmaf(vi, vi, 4.f * kappa));
+    float e, d;
+    dbk2(vi, kappa, r, e, d);
+    C.E[i] = e;
+    C.D[i] = d;
+    C.c[i] = 1.f / r;
+    return vi > 0.f;
+  });
   if (nb > kb) {
     // more candidates than border slots: keep the kb largest v (ties by row
-    // index) and eliminate the rest.  The rank of row i counts the rows
-    // ahead of it; v is read four rows per 16-byte broadcast load, several
-    // loads in flight, and the padding past row m is masked.
-    li *cand = C.role;
-    const lf4 *v4 = reinterpret_cast<const lf4 *>(C.v);
-    const int m4 = (m + 3) >> 2;
+    // index) and eliminate the rest.  The rank of a candidate counts those
+    // ahead of it, read four per 16-byte broadcast load (the list's padding
+    // is masked).
+    const lf4 *v4 = reinterpret_cast<const lf4 *>(C.t0);
+    const int nq = (nb + 3) >> 2, cnt = nb;
     for (int i = tid; i < m; i += T) {
-      int f = 0;
-      const float vi = C.v[i];
-      if (vi > 0.f) {
+      const int k = C.role[i];
+      if (k >= 0) {
+        const float vi = C.v[i];
         int rank = 0;
         auto ahead = [&](float vj, int j) {
-          return (int)(j < m && ((vj > vi) || (vj == vi && j < i)));
+          return (int)(j < cnt && ((vj > vi) || (vj == vi && j < k)));
         };
 #pragma unroll 4
-        for (int q = 0; q < m4; ++q) {
+        for (int q = 0; q < nq; ++q) {
           const f4v w4 = v4[q];
           rank += ahead(w4.x, 4 * q) + ahead(w4.y, 4 * q + 1) + ahead(w4.z, 4 * q + 2) +
                   ahead(w4.w, 4 * q + 3);
         }
-        f = rank < kb;
+        if (rank >= kb) C.role[i] = -1;
       }
-      cand[i] = f;
     }
     __syncthreads();
-    nb = compact_rows<T>(cand, m, C.bidx, C.red);
-    for (int i = tid; i < m; i += T) cand[i] = !cand[i];
-    __syncthreads();
-    ne = compact_rows<T>(cand, m, C.elist, C.red);
-    for (int i = tid; i < m; i += T) C.role[i] = -1;
-    __syncthreads();
-    for (int k = tid; k < nb; k += T) C.role[C.bidx[k]] = k;
+    lists([&](int i) { return C.role[i] >= 0; });
   }
   if (tid == 0) C.iflag[1] = ne;
   __syncthreads();
@@ -1999,19 +2017,23 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
   // (coalesced cooperative loads), then each tile thread reads its 4 + 4
   // entries per row as 16-byte LDS loads.  The staging area is the (not yet
   // written) border part of M when M is in LDS, else the `part` buffer.
-  const int ldg = al4(n);
-  lf *stage = C.part;
-  int cap = 2 * T;
-  if constexpr (std::is_same<typename CT::MT, lf>::value) {
-    const int room = moff(N) - moff(n);
-    if (room > cap) { stage = C.M + moff(n); cap = room; }
-  }
-  const int R = max(1, cap / ldg);
   const int nt = (n + 3) >> 2;
   const int ntiles = nt * (nt + 1) / 2;
   // tile threads are split into `groups` that take every groups-th staged
   // row; group 0 writes Q + its sum, the others add theirs in a fixed order
   const int groups = 1 + (2 * ntiles <= T) + (3 * ntiles <= T) + (4 * ntiles <= T);
+  const int ldg = al4(n);
+  lf *stage = C.part;
+  int cap = 2 * T;
+  if constexpr (std::is_same<MT, lf>::value) {
+    const int room = moff(N) - moff(n);
+    if (room > cap) { stage = C.M + moff(n); cap = room; }
+  } else if (groups == 1) {
+    // one group takes every row in order, whatever the chunks: the whole span
+    // of idle vectors (n = 65: 35 rows at a time instead of 7)
+    cap = make_layout(n, C.m, p, C.kb, false, T).stg_len;
+  }
+  const int R = max(1, cap / ldg);
   for (int tb = 0; tb < ntiles; tb += T) {
     // with more than one group, tb = 0: group g has threads g ntiles ..
     const int g = groups > 1 ? (tid >= ntiles) + (tid >= 2 * ntiles) + (tid >= 3 * ntiles) +
@@ -2166,7 +2188,7 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
       for (int u = 0; u < 4; ++u) {
         const int k = k0 + u * NG + grp;
         if (k0 + u * NG < K) {
-          border_exponent(C.dinv, n + min(k, K - 1), k < K, sub, ss[u], el);
+          border_exponent(C.ex, n + min(k, K - 1), k < K, sub, ss[u], el);
           if (k < K) {
             const MRow<MT> row = mrow<MT>(N, n + k);
             for (int l = sub; l < k; l += 16) M[row.at(n + l)] = 0.f;
@@ -2188,19 +2210,12 @@ QPK_PHASE void assemble(CT &Cin_, int nb, int ne, const lf *wts, bool bounded, f
   QPK_PT(PH_ASM_BORDER);
 }
 
-// dinv[j] = 1 / L[j][j]
-template <int T, class CT>
-QPD void make_dinv(CT &C, int N) {
-  for (int j = tidx(); j < N; j += T) C.dinv[j] = 1.f / C.M[mrow<typename CT::MT>(N, j).at(j)];
-  __syncthreads();
-}
-
 // Solve for u0 or both right-hand sides u0 and u1.
 template <int T, int RPL, class CT>
 QPK_PHASE void solve2(CT &Cin_, int N, bool both) {
   CT C = uctx(Cin_);
   N = rfl(N); both = rfl(both);
-  signed_solve<T, RPL>(C.M, N, C.n, C.dinv, C.u0, C.u1, both, C.mz, C.part);
+  signed_solve<T, RPL>(C.M, N, C.n, C.u0, C.u1, both, C.mz, C.part, C.iflag + 6);
   __syncthreads();
 }
 
@@ -2307,7 +2322,7 @@ QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int s
     }
     if (it == steps) break;
     prev = nrm;
-    signed_solve<T, RPL>(C.M, N, n, C.dinv, r, r, false, C.mz, C.part);
+    signed_solve<T, RPL>(C.M, N, n, r, r, false, C.mz, C.part, C.iflag + 6);
     __syncthreads();
     for (int j = tid; j < N; j += T) {
       C.rd[j] = r[j];
@@ -2407,7 +2422,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     border_delta<T>(C, nb, delta_rel, 0.f);
   }
   QPK_PT(PH_ASM_DIAG);
-  bool ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, C.dyn != 0, C.part, C.dinv);
+  bool ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, C.dyn != 0, C.part, C.ex);
   QPK_PT(PH_FACT);
   *regularised = delta_rel > 0.f || floor || C.iflag[2] > 0;
   if (!ok && C.dyn) {
@@ -2416,7 +2431,7 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
     const float pmax = __int_as_float(C.iflag[4]);
     assemble<T>(C, nb, ne, wts, true, 0.f);
     border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * pmax);
-    ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, true, C.part, C.dinv);
+    ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, true, C.part, C.ex);
     *regularised = true;
   }
   return ok;
@@ -2557,8 +2572,7 @@ QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
   const int ne = compact_rows<T>(C.role, m, C.elist, C.red);
   assemble<T>(C, 0, ne, C.E, false, 0.f);
   const int N = n + p;
-  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, dyn, C.part, C.dinv);
-  make_dinv<T>(C, N);
+  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, dyn, C.part, C.ex);
   if (m) {
     const lf *hv[1] = {C.h};
     lf *o[1] = {C.tGz};
@@ -2595,19 +2609,22 @@ QPK_PHASE bool initialize(CT &Cin_, double &work, bool dyn) {
     }
   }
   __syncthreads();
-  const double dn = n, dm = m, dN = N;
-  work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0 + 2.0 * dN * dN + 4.0 * dm * dn;
-  work += nref0 * (2.0 * dN * dN + 2.0 * dn * dn);  // refinement steps
+  if (C.wk) {
+    const double dn = n, dm = m, dN = N;
+    work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0 + 2.0 * dN * dN + 4.0 * dm * dn;
+    work += nref0 * (2.0 * dN * dN + 2.0 * dn * dn);  // refinement steps
+  }
   return ok;
 }
 
 // One Newton iteration of the bounded (implicit) form.  Mode of the target:
 // kt_mode 0 = predictor-corrector, 1 = fixed sigma, 2 = relax (kt = kr).
 // Returns a status code (ST_CONV meaning "keep going"), with the stage in
-// *stage on failure.  Updates x, y, v, kappa, z, s.
+// *stage on failure.  Updates x, y, v, kappa, z, s; sz receives this thread's
+// part of the new s'z (v and sz are what the next iteration starts from).
 template <int T, int RPL, class CT>
 QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, float kr,
-                       float delta_reg, int refine_steps, double &work, int *stage) {
+                       float delta_reg, int refine_steps, double &work, int *stage, float &sz) {
   CT C = uctx(Cin_);
   kappa = rflf(kappa); kt_mode = rfl(kt_mode); sigma = rflf(sigma); kr = rflf(kr);
   delta_reg = rflf(delta_reg); refine_steps = rfl(refine_steps);
@@ -2617,8 +2634,12 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
   const int ne = C.iflag[1];
   QPK_PT(PH_PART);
   const int N = n + nb + p;
-  const double dn = n, dm = m, dp = p, dN = N;
-  work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;            // residuals
+  auto count = [&](auto flops) {  // algorithmic flops
+    if (C.wk) work += flops((double)n, (double)m, (double)p, (double)N);
+  };
+  count([](double dn, double dm, double dp, double) {  // residuals
+    return 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;
+  });
   // Factor, solve and refine.  With split-product (BF16x3) assembly, a
   // refinement that contracts by less than kRefineSlow per step means the
   // assembly error is too large for this system's conditioning: the QP
@@ -2631,11 +2652,14 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     __syncthreads();
     bool reg = false;
     ok = factor_bounded<T, RPL>(C, nb, ne, C.t1, delta_reg, &reg, floor);
-    work += (double)ne * dn * (dn + 1.0) + dN * dN * dN / 3.0;      // assembly + factor
-    work += 2.0 * (2.0 * dN * dN + 4.0 * dm * dn);                  // two solves
+    count([&](double dn, double, double, double dN) {  // assembly + factor
+      return (double)ne * dn * (dn + 1.0) + dN * dN * dN / 3.0;
+    });
+    count([](double dn, double dm, double, double dN) {  // two solves
+      return 2.0 * (2.0 * dN * dN + 4.0 * dm * dn);
+    });
     if (!ok) break;
-    make_dinv<T>(C, N);
-    QPK_PT(PH_DINV);
+    if (tid == 0) C.iflag[6] = 0;  // (barriers in the right-hand sides)
     rhs_bounded<T>(C, nb, kappa, nullptr, nullptr, nullptr, false);
     QPK_PT(PH_RHS);
     const int nref = (reg || C.amode == 1) ? max(refine_steps, 2)
@@ -2649,7 +2673,9 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     if (nref) {
       const float q0 = refine_policy<T, RPL>(C, nb, true, C.w0, C.u0, nref);
       const float q1 = refine_policy<T, RPL>(C, nb, true, C.w1, C.u1, nref);
-      work += 2.0 * nref * (2.0 * dN * dN + 4.0 * dm * dn + 2.0 * dn * dn + 4.0 * dp * dn);
+      count([&](double dn, double dm, double dp, double dN) {
+        return 2.0 * nref * (2.0 * dN * dN + 4.0 * dm * dn + 2.0 * dn * dn + 4.0 * dp * dn);
+      });
       if (C.amode == 1 && !(fmaxf(q0, q1) <= kRefineSlow)) {
         C.amode = 2;
         if (tid == 0) C.iflag[3] = 2;
@@ -2659,7 +2685,9 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     }
     // a factor that passed its checks can still give a non-finite solution
     // when it is nearly singular: redo the step once with a border floor
-    if (C.dyn && !floor && any_nonfinite<T>(C.u0, C.u1, true, N, C.red)) {
+    // (the solving waves have seen whether theirs is; a refinement may change it)
+    if (C.dyn && !floor &&
+        (nref ? any_nonfinite<T>(C.u0, C.u1, true, N, C.red) : C.iflag[6] != 0)) {
       floor = true;
       continue;
     }
@@ -2725,11 +2753,16 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
   // every inactive row would then be 0 and the next centering would divide
   // by kappa = 0.  Held at the bound the step cannot cross.
   const float knew = fmaxf(kappa + alpha * dk, fminf(kt, kappa));
+  sz = 0.f;
   for (int i = tid; i < m; i += T) {
     const float vn = C.v[i] + alpha * fmaf(kt, C.dv1[i], C.dv0[i]);
-    C.v[i] = vn;
-    C.z[i] = bk(vn, knew);
-    C.s[i] = bk(-vn, knew);
+    float zn, sn;
+    bk2(vn, knew, zn, sn);
+    C.z[i] = zn;
+    C.s[i] = sn;
+    // the next iteration's manifold coordinate and its share of s'z
+    C.v[i] = zn - sn;
+    sz += sn * zn;
   }
   kappa = knew;
   __syncthreads();
@@ -2759,13 +2792,14 @@ QPK_PHASE int newton_standard(CT &Cin_, float mu, int kt_mode, float kr, float d
   __syncthreads();
   const int N = n + p;
   assemble<T>(C, 0, ne, C.E, false, delta_reg);
-  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.dinv);
-  const double dn = n, dm = m, dp = p, dN = N;
-  work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;
-  work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0;
-  work += 2.0 * (2.0 * dN * dN + 4.0 * dm * dn);
+  const bool ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.ex);
+  if (C.wk) {
+    const double dn = n, dm = m, dp = p, dN = N;
+    work += 2.0 * dn * dn + 4.0 * dm * dn + 4.0 * dp * dn;
+    work += dm * dn * (dn + 1.0) + dN * dN * dN / 3.0;
+    work += 2.0 * (2.0 * dN * dN + 4.0 * dm * dn);
+  }
   if (!ok) { *stage = SG_PRED; return ST_FACT; }
-  make_dinv<T>(C, N);
   // rhs for a given r_c / s =: q_i;  u_x = -r_t - G'(w r_i - q), u_y = -r_e
   // then dz = w (r_i + G dx) - q, ds = -r_i - G dx
   auto rhs_and_solve = [&](const lf *qv) {
@@ -2882,14 +2916,18 @@ QPD int newton_loop(CT &Cin_, bool bounded, int max_iter, float tol, int kt_mode
                     float &res) {
   int status = ST_MAXIT;
   int stage = SG_NONE;
+  float sz = 0.f;
   for (int it = 0;; ++it) {
     CT C = uctx(Cin_);
     const int m = C.m, tid = tidx();
     // manifold coordinates v = z - s, kappa = s'z / m
-    float sm[1] = {0.f};
-    for (int i = tid; i < m; i += T) {
-      sm[0] += C.s[i] * C.z[i];
-      if (bounded) C.v[i] = C.z[i] - C.s[i];
+    float sm[1] = {sz};
+    if (it == 0 || !bounded) {
+      sm[0] = 0.f;
+      for (int i = tid; i < m; i += T) {
+        sm[0] += C.s[i] * C.z[i];
+        if (bounded) C.v[i] = C.z[i] - C.s[i];
+      }
     }
     block_reduce<T, OpSum, 1>(sm, C.red);
     float kappa = m ? sm[0] / (float)m : 0.f;
@@ -2923,7 +2961,8 @@ QPD int newton_loop(CT &Cin_, bool bounded, int max_iter, float tol, int kt_mode
     }
     int st;
     if (bounded)
-      st = newton_bounded<T, RPL>(C, kappa, kt_mode, sigma, kr, delta_reg, refine_steps, work, &stage);
+      st = newton_bounded<T, RPL>(C, kappa, kt_mode, sigma, kr, delta_reg, refine_steps, work, &stage,
+                                  sz);
     else st = newton_standard<T, RPL>(C, kappa, kt_mode, kr, delta_reg, work, &stage);
     if (st != ST_CONV) {
       status = st;
@@ -2991,9 +3030,14 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     for (int i = tid; i < m; i += T) C.E[i] = C.t1[i];
   __syncthreads();
   const int N = n + nb + p;
-  const double dn = n, dN = N;
-  const double wfac = (double)ne * dn * (dn + 1.0) + dN * dN * dN / 3.0 + 2.0 * dN * dN + 8.0 * m * dn;
-  const double wstep = 2.0 * dN * dN + 2.0 * dn * dn + 8.0 * m * dn + 4.0 * p * dn;
+  auto count = [&](int nref) {  // algorithmic flops
+    if (C.wk) {
+      const double dn = n, dN = N;
+      const double wfac = (double)ne * dn * (dn + 1.0) + dN * dN * dN / 3.0 + 2.0 * dN * dN + 8.0 * m * dn;
+      const double wstep = 2.0 * dN * dN + 2.0 * dn * dn + 8.0 * m * dn + 4.0 * p * dn;
+      work += wfac + nref * wstep;
+    }
+  };
   bool ok = false, inaccurate = false;
   if (bounded) {
     C.amode = rfl(C.iflag[3]);
@@ -3012,9 +3056,8 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
       // split-product factor is always refined against the exact operator
       const int nref = (reg || C.amode == 1) ? max(refine_steps, 2)
                                              : plain_refine_steps(C.rmode, refine_steps, 2);
-      work += wfac + nref * wstep;
+      count(nref);
       if (!ok) break;
-      make_dinv<T>(C, N);
       rhs_bounded<T>(C, nb, kappa, gx, gz, gy, true);
       for (int j = tid; j < N; j += T) C.w0[j] = C.u0[j];
       __syncthreads();
@@ -3041,11 +3084,10 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     for (int i = tid; i < m; i += T) C.dv0[i] = C.E[i] * (C.dv0[i] + (gz ? gz[i] : 0.f));
   } else {
     assemble<T>(C, nb, ne, C.t1, false, 0.f);
-    ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.dinv);
+    ok = signed_cholesky<T, RPL>(C.M, N, n, C.iflag, false, C.part, C.ex);
     const int nref = plain_refine_steps(C.rmode, refine_steps, 2);
-    work += wfac + nref * wstep;
+    count(nref);
     if (!ok) return kAdjFactorFail;
-    make_dinv<T>(C, N);
     // standard: [H A'; A 0][a; c] = [-gx - G' W gz; -gy], dz = W (G a + gz)
     for (int i = tid; i < m; i += T) C.t0[i] = gz ? C.E[i] * gz[i] : 0.f;
     __syncthreads();
@@ -3180,6 +3222,7 @@ QPD void qp_body(const Params &P) {
   C.dyn = P.form == 0;
   C.rmode = P.rmode;
   C.bo = P.backoff;
+  C.wk = MODE != kServe && P.work != nullptr;
   if (tid == 0) {
     C.iflag[5] = 0;  // refinement residuals start in FP32
   }
