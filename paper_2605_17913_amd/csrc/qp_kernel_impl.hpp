@@ -235,7 +235,11 @@ QPD V wave_bfly(V v) {
   return row_bfly<Op>(v);
 }
 
-// Reduce K values across the workgroup; every thread gets the results.
+// Reduce K values across the workgroup; every thread gets the results, as
+// scalars: read from LDS they count as different per lane, and a Newton loop
+// that leaves on such a value is compiled as a divergent one, with its
+// uniform state (sizes, addresses) in vector registers that spill and are
+// reloaded one by one in every iteration.
 // `red` needs (T/64)*K floats.  Contains two barriers.
 template <int T, class Op, int K>
 QPD void block_reduce(float (&v)[K], lf *red) {
@@ -255,7 +259,7 @@ QPD void block_reduce(float (&v)[K], lf *red) {
       float r = red[k];
 #pragma unroll
       for (int i = 1; i < T / 64; ++i) r = Op::f(r, red[i * K + k]);
-      v[k] = r;
+      v[k] = rflf(r);
     }
     __syncthreads();
   }
@@ -805,7 +809,7 @@ QPD int border_emax(const li *flag) {
   int e = kNoExp;
 #pragma unroll
   for (int w = 0; w < T / 64; ++w) e = max(e, flag[8 + w]);
-  return e;
+  return rfl(e);
 }
 QPD int border_shift(const lf *ex, int i, int emax) {
   const int e = __float_as_int(ex[i]);
@@ -1011,8 +1015,8 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     flag[4] = __float_as_int(pmax);  // largest accepted pivot (retry scale)
   }
   __syncthreads();
-  bool good = flag[0] == 0;
-  if (flag[2] > 0) {
+  bool good = rfl(flag[0]) == 0;
+  if (rfl(flag[2]) > 0) {
     // with regularised pivots, entries of L far beyond the scale sqrt(pmax)
     // of a stable factor mean the replaced pivots amplified rounding errors:
     // report a failure so the caller factors again with a uniform floor
@@ -1028,7 +1032,8 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
     if (lane == 0) flag[8 + wid] = __float_as_int(lmax);
     __syncthreads();
     for (int w = 0; w < NW; ++w) lmax = fmaxf(lmax, __int_as_float(flag[8 + w]));
-    if (!(lmax <= kGrowthMax * sqrtf(__int_as_float(flag[4])))) good = false;
+    lmax = rflf(lmax);
+    if (!(lmax <= kGrowthMax * sqrtf(__int_as_float(rfl(flag[4]))))) good = false;
   }
   if (eq) {
     if (wid == 0) {
@@ -1716,7 +1721,7 @@ QPD int compact_rows(const li *flag, int m, li *out, lf *red) {
       tot += c;
     }
     if (f) out[base + off + pre] = i;
-    base += tot;
+    base += rfl(tot);
     __syncthreads();
   }
   return base;
@@ -1768,8 +1773,8 @@ QPK_PHASE int partition_bounded(CT &Cin_, float kappa) {
           C.role[i] = -1;
         }
       }
-      nb += tb;
-      ne += te;
+      nb += rfl(tb);
+      ne += rfl(te);
       __syncthreads();
     }
   };
@@ -2343,7 +2348,7 @@ QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int s
 template <int T, int RPL, class CT>
 QPD float refine_policy(CT &C, int nb, bool bounded, const lf *w, lf *u, int steps) {
   float q;
-  if (C.rmode == 1 || C.iflag[5]) {
+  if (C.rmode == 1 || rfl(C.iflag[5])) {
     q = refine<T, RPL, double>(C, nb, bounded, w, u, steps);
   } else {
     q = refine<T, RPL, float>(C, nb, bounded, w, u, steps);
@@ -2417,18 +2422,18 @@ QPD bool factor_bounded(CT &C, int nb, int ne, const lf *wts, float delta_rel, b
   if (floor) {
     // asked for by a caller whose solve came out non-finite: floor the
     // border at the scale of the previous factorisation's pivots
-    border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * __int_as_float(C.iflag[4]));
+    border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * __int_as_float(rfl(C.iflag[4])));
   } else if (delta_rel > 0.f) {
     border_delta<T>(C, nb, delta_rel, 0.f);
   }
   QPK_PT(PH_ASM_DIAG);
   bool ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, C.dyn != 0, C.part, C.ex);
   QPK_PT(PH_FACT);
-  *regularised = delta_rel > 0.f || floor || C.iflag[2] > 0;
+  *regularised = delta_rel > 0.f || floor || rfl(C.iflag[2]) > 0;
   if (!ok && C.dyn) {
     // the floor is at least kRetryReg times the largest pivot the failed
     // attempt accepted, i.e. scaled like the Schur complement's entries
-    const float pmax = __int_as_float(C.iflag[4]);
+    const float pmax = __int_as_float(rfl(C.iflag[4]));
     assemble<T>(C, nb, ne, wts, true, 0.f);
     border_delta<T>(C, nb, fmaxf(delta_rel, 1e-6f), kRetryReg * pmax);
     ok = signed_cholesky<T, RPL>(C.M, N, C.n, C.iflag, true, C.part, C.ex);
@@ -2555,7 +2560,7 @@ QPD int mkstatus(int st, int stage) { return st | (stage << 8); }
 // FP32.
 template <class CT>
 QPD int precision_bits(const CT &C, int amode0) {
-  return (C.iflag[5] ? 1 << 16 : 0) | (amode0 == 1 && C.iflag[3] != 1 ? 1 << 17 : 0);
+  return (rfl(C.iflag[5]) ? 1 << 16 : 0) | (amode0 == 1 && C.iflag[3] != 1 ? 1 << 17 : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2631,7 +2636,7 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
   const int n = C.n, m = C.m, p = C.p, tid = tidx();
   C.amode = rfl(C.iflag[3]);  // this QP's assembly arithmetic (may have fallen back)
   const int nb = partition_bounded<T>(C, kappa);
-  const int ne = C.iflag[1];
+  const int ne = rfl(C.iflag[1]);
   QPK_PT(PH_PART);
   const int N = n + nb + p;
   auto count = [&](auto flops) {  // algorithmic flops
@@ -2687,7 +2692,7 @@ QPK_PHASE int newton_bounded(CT &Cin_, float &kappa, int kt_mode, float sigma, f
     // when it is nearly singular: redo the step once with a border floor
     // (the solving waves have seen whether theirs is; a refinement may change it)
     if (C.dyn && !floor &&
-        (nref ? any_nonfinite<T>(C.u0, C.u1, true, N, C.red) : C.iflag[6] != 0)) {
+        (nref ? any_nonfinite<T>(C.u0, C.u1, true, N, C.red) : rfl(C.iflag[6]) != 0)) {
       floor = true;
       continue;
     }
@@ -2935,7 +2940,7 @@ QPD int newton_loop(CT &Cin_, bool bounded, int max_iter, float tol, int kt_mode
     bool bad = false;
     // FP64 residuals under the FP64 policy, and for a QP whose refinement
     // has already needed FP64 (FP32 cannot resolve its residuals either)
-    const bool r64 = C.rmode == 1 || (C.rmode == 0 && C.iflag[5] != 0);
+    const bool r64 = C.rmode == 1 || (C.rmode == 0 && rfl(C.iflag[5]) != 0);
     res = r64 ? residuals<T, double>(C, bounded, kappa, kt_mode == 2 ? kr : 0.f, &bad)
               : residuals<T, float>(C, bounded, kappa, kt_mode == 2 ? kr : 0.f, &bad);
     QPK_PT(PH_RESID);
@@ -3013,7 +3018,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
   int nb = 0, ne = 0;
   if (bounded && m) {
     nb = partition_bounded<T>(C, kappa);
-    ne = C.iflag[1];
+    ne = rfl(C.iflag[1]);
     for (int i = tid; i < m; i += T) C.t1[i] = C.E[i] / C.D[i];
   } else {
     for (int i = tid; i < m; i += T) {
@@ -3065,7 +3070,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
       solve2<T, RPL>(C, N, false);
       const float q = nref ? refine_policy<T, RPL>(C, nb, true, C.w0, C.u0, nref) : 0.f;
       inaccurate = nref && !(q <= kRefineSlow) &&
-                   !(__int_as_float(C.iflag[7]) <= kAdjResTol * wn);
+                   !(__int_as_float(rfl(C.iflag[7])) <= kAdjResTol * wn);
       if (C.amode == 1 && !(q <= kRefineSlow)) {
         C.amode = 2;
         if (tid == 0) C.iflag[3] = 2;
@@ -3103,7 +3108,7 @@ QPK_PHASE int adjoint(CT &Cin_, bool bounded, const gf *gx, const gf *gy, const 
     solve2<T, RPL>(C, N, false);
     if (nref) {
       const float q = refine_policy<T, RPL>(C, 0, false, C.w0, C.u0, nref);
-      inaccurate = !(q <= kRefineSlow) && !(__int_as_float(C.iflag[7]) <= kAdjResTol * wn);
+      inaccurate = !(q <= kRefineSlow) && !(__int_as_float(rfl(C.iflag[7])) <= kAdjResTol * wn);
     }
     if (m) {
       const lf *xv[1] = {C.u0};
@@ -3284,7 +3289,7 @@ QPD void qp_body(const Params &P) {
       out[n + p + m + i] = C.s[i];
     }
     __syncthreads();
-    if (tid == 0) st[sticky] = __int_as_float((C.iflag[3] & 3) | ((C.iflag[5] & 1) << 2));
+    if (tid == 0) st[sticky] = __int_as_float((C.iflag[3] & 3) | ((rfl(C.iflag[5]) & 1) << 2));
     if (tid == 0) {
       *d.status = status | precision_bits(C, amode0);
       *d.iters = iters;
