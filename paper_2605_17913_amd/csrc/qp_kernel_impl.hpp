@@ -1980,25 +1980,31 @@ QPD void assemble_h_mfma(CT &C, int N, int ne, const lf *wts) {
       }
     }
     // result layout: register r of lane l is row 4(l/16) + r, column l%16;
-    // all of Q's entries before the stores
-    f4v qv[kAsmTiles];
+    // Q's entries of kQ tiles before their stores
+    constexpr int kQ = T >= 512 ? 6 : 3;
 #pragma unroll
-    for (int j = 0; j < kAsmTiles; ++j) {
-      if (!val[j]) continue;
-      const int col = 16 * tj[j] + c16;
+    for (int j0 = 0; j0 < kAsmTiles; j0 += kQ) {
+      f4v qv[kQ];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        qv[j][r] = C.Q[(unsigned)(min(16 * ti[j] + 4 * g + r, n - 1) * n + min(col, n - 1))];
-    }
+      for (int i = 0; i < kQ; ++i) {
+        const int j = j0 + i;
+        if (j >= kAsmTiles || !val[j]) continue;
+        const int col = 16 * tj[j] + c16;
 #pragma unroll
-    for (int j = 0; j < kAsmTiles; ++j) {
-      if (!val[j]) continue;
-      const int col = 16 * tj[j] + c16;
+        for (int r = 0; r < 4; ++r)
+          qv[i][r] = C.Q[(unsigned)(min(16 * ti[j] + 4 * g + r, n - 1) * n + min(col, n - 1))];
+      }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * ti[j] + 4 * g + r;
-        if (row < n && col <= row)
-          M[mrow<typename CT::MT>(N, row).at(col)] = qv[j][r] + acc[j][r];
+      for (int i = 0; i < kQ; ++i) {
+        const int j = j0 + i;
+        if (j >= kAsmTiles || !val[j]) continue;
+        const int col = 16 * tj[j] + c16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * ti[j] + 4 * g + r;
+          if (row < n && col <= row)
+            M[mrow<typename CT::MT>(N, row).at(col)] = qv[i][r] + acc[j][r];
+        }
       }
     }
   }
