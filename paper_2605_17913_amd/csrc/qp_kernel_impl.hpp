@@ -365,8 +365,10 @@ __host__ __device__ inline Layout make_layout(int n, int m, int p, int kb, bool 
   const int sn = al4(n), sm = al4(max(m, 1)), sp = al4(max(p, 1)), sN = al4(L.Nmax);
   const int st = al4(max(max(m, p), L.Nmax));  // t0, t1: also m- and p-vectors
   L.iflag = 0;
-  // partial sums: 2 floats or 1 double per thread
-  L.part = 16; L.red = L.part + 2 * T;
+  // partial sums: 2 floats or 1 double per thread (4 floats before them are
+  // unused: the plans' LDS bound, and with it the border cap of sizes at the
+  // bound, counts them)
+  L.part = 20; L.red = L.part + 2 * T;
   const int b0 = L.red + (T / 64) * 16;
   L.u0 = b0; L.u1 = b0 + sN; L.rr = b0 + 2 * sN; L.rd = b0 + 3 * sN;
   L.dv0 = b0 + 4 * sN; L.dv1 = L.dv0 + sm;
