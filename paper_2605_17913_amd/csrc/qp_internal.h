@@ -76,8 +76,8 @@ int64_t ws_floats(int n, int m, int p, int kb);
 // Whether the matrix-core assembly's LDS staging fits the per-QP layout.
 bool mfma_stage_fits(int n, int m, int p, int kb, bool m_in_lds, int threads);
 // Largest dynamic LDS per block the kernels may use on this device.
-// LDS of a CU, the kernels' static LDS (context table, profiling counters;
-// an upper bound) and the most dynamic LDS one QP may take.
+// LDS of a CU, the kernels' static LDS (profiling counters; an upper
+// bound, which the sizes that fit LDS depend on) and the most dynamic LDS one QP may take.
 constexpr size_t kCuLds = 160 * 1024;
 #ifdef QPK_PHASE_TIMING
 constexpr size_t kStaticLds = 512 + 256;

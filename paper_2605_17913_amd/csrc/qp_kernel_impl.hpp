@@ -702,7 +702,8 @@ QPD float row_max_before(float x) {
 // maximum across the lanes.  If one needs a decision, the return value is
 // true, pmax and pmaxh are unchanged, and the caller repeats the panel from
 // its saved tiles with eliminate_checked().  Alone on a CU a panel takes 5.7K
-// cycles decided pivot by pivot, 1.7K here.  Rows past the last column
+// cycles decided pivot by pivot, 2.6K here (the lane broadcasts, two vector
+// instructions per multiplier with its update, are most of that).  Rows past the last column
 // (kb < 16) are replaced by rows of the identity first, whose pivots are 1
 // and whose multipliers are 0.
 QPD bool eliminate(float (&P)[kNB], float (&iv)[kNB], int k0, int kb, int npos, float &pmax,
@@ -1259,7 +1260,7 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
 // taken in turn), one barrier, and the other waves' subtractions.  One wave per
 // right-hand side, each reading the factor with a row per lane, spent 7K
 // cycles per block on the 64 cache lines of every load (n = 256); this takes
-// about 1K.
+// 3.5K there and 2.2K at n = 100.
 template <int T, int RPL>
 QPD void signed_solve_tiles(const gf *M, int N, int npos, lf *r0, lf *r1, bool both,
                             lf *ex, li *bad) {
