@@ -694,6 +694,12 @@ QPD float row_max_before(float x) {
 #undef QPK_SHR
 }
 
+// A panel of at most kFewCols columns (the last one) is eliminated column by
+// column: eliminate() runs all 16 of its steps whatever the panel holds.  At 5
+// to 8 columns the short form takes up to 2% longer; at 1 or 2 (2048 QPs of
+// n = 1, m = 1) it takes 291 us and the other 307.
+constexpr int kFewCols = 4;
+
 // The same elimination for a panel whose pivots are all good (positive,
 // finite and above kPivTol times the largest before them: the common case).
 // The chain from one pivot to the next bounds the factorisation of every
@@ -965,7 +971,7 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
       }
       float P[kNB], iv[kNB];
       tiles_to_rows(t, P);
-      if (eliminate(P, iv, k0, kb, npos, pmax, pmaxh)) {
+      if (kb <= kFewCols || eliminate(P, iv, k0, kb, npos, pmax, pmaxh)) {
         tiles_to_rows(t, P);
         fail |= eliminate_checked(P, iv, k0, kb, npos, dyn, pmax, pmaxh, nreg);
       }
@@ -1147,9 +1153,14 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
       for (int t = 0; t < S; ++t) e[S * (lane - l0) + t] = a[t];
     }
   };
+  // With a row per lane, a last block of at most kFewCols rows takes that many
+  // steps instead of 16 (QPs of a few rows are nothing but that block: 2048 of
+  // n = 1, m = 1 291 -> 283 us).
+  const bool few = S == 1 && WG == 1 && N - kNB * (nblk - 1) <= kFewCols;
+  const int whole = nblk - (few ? 1 : 0), lf0 = (kNB / S) * whole;
   load_f(0);
 #pragma unroll 1
-  for (int b = 0; b < nblk; ++b) {
+  for (int b = 0; b < whole; ++b) {
     const int l0 = (kNB / S) * (b / WG);
     const bool own = WG == 1 || b % WG == g;
     lf *e = ex + 16 * (b & 1);
@@ -1182,6 +1193,11 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
       }
     }
   }
+  if (few) {
+    take();
+#pragma unroll
+    for (int c = 0; c < kFewCols; ++c) step(0, c, lf0);
+  }
   // sign: w <- sg w
 #pragma unroll
   for (int t = 0; t < S; ++t)
@@ -1205,8 +1221,14 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
     }
   };
   load_b(kNB * nblk - CW);
+  if (few) {
+    take();
+    load_b(max(kNB * whole - CW, 0));
+#pragma unroll
+    for (int c = kFewCols - 1; c >= 0; --c) step(0, c, lf0);
+  }
 #pragma unroll 1
-  for (int b = nblk - 1; b >= 0; --b) {
+  for (int b = whole - 1; b >= 0; --b) {
     const int l0 = (kNB / S) * (b / WG);
     const bool own = WG == 1 || b % WG == g;
     // (not the buffer of the forward sweep's last step: it may still be read)
