@@ -12,6 +12,9 @@
 
 #include "../../include/qpx.h"
 #include "qp_internal.h"
+#ifdef QPK_PHASE_TIMING
+#include "qp_phase.h"
+#endif
 
 namespace {
 
@@ -95,7 +98,7 @@ void fill_common(qpk::Params &P, const qp_batch *bt, const qp_opts &o, const qpk
 static void phase_report(const char *what, qpk::Params &P, hipStream_t st, bool before) {
   static long long *buf = nullptr;
   static size_t cap = 0;
-  const size_t need = (size_t)P.B * 32;
+  const size_t need = (size_t)P.B * PH_N;
   if (before) {
     if (need > cap) {
       if (buf) (void)hipFree(buf);
@@ -110,18 +113,15 @@ static void phase_report(const char *what, qpk::Params &P, hipStream_t st, bool 
   (void)hipStreamSynchronize(st);
   long long *h = new long long[need];
   (void)hipMemcpy(h, buf, need * sizeof(long long), hipMemcpyDeviceToHost);
-  static const char *names[32] = {"init", "resid", "part", "asm", "fact", "rhs", "solve",
-                                  "refine", "recover", "step", "bwd", "out", "asm_border",
-                                  "asm_diag", "fact_update", "fact_elim", "dinv", "matvec",
-                                  "kappa", "affine", "refine_apply"};
-  double tot[32] = {0};
+  double tot[PH_COUNT] = {0};
   for (size_t i = 0; i < (size_t)P.B; ++i)
-    for (int k = 0; k < 31; ++k) tot[k] += (double)h[i * 32 + k];
+    for (int k = 0; k < PH_COUNT; ++k) tot[k] += (double)h[i * PH_N + k];
   double all = 0;
-  for (int k = 0; k < 31; ++k) all += tot[k];
+  for (int k = 0; k < PH_COUNT; ++k) all += tot[k];
   fprintf(stderr, "QPK_PHASES %s B=%d cycles/QP=%.0f", what, P.B, all / P.B);
-  for (int k = 0; k < 31; ++k)
-    if (tot[k] > 0) fprintf(stderr, " %s=%.0f (%.1f%%)", names[k], tot[k] / P.B, 100.0 * tot[k] / all);
+  for (int k = 0; k < PH_COUNT; ++k)
+    if (tot[k] > 0)
+      fprintf(stderr, " %s=%.0f (%.1f%%)", kPhaseNames[k], tot[k] / P.B, 100.0 * tot[k] / all);
   fprintf(stderr, "\n");
   delete[] h;
 }

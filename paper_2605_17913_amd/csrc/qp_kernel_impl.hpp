@@ -47,6 +47,9 @@
 #include <type_traits>
 
 #include "qp_internal.h"
+#ifdef QPK_PHASE_TIMING
+#include "qp_phase.h"
+#endif
 
 namespace qpk {
 namespace {
@@ -144,11 +147,8 @@ QPD void wave_sync() {
 // thread 0 accumulates clock64() deltas per phase in LDS (a workgroup barrier
 // at every mark); the kernel writes them to Params::phase.  Compiled out
 // otherwise.
-enum Phase { PH_INIT, PH_RESID, PH_PART, PH_ASM, PH_FACT, PH_RHS, PH_SOLVE, PH_REFINE,
-             PH_RECOVER, PH_STEP, PH_BWD, PH_OUT, PH_ASM_BORDER, PH_ASM_DIAG, PH_FACT_UPDATE,
-             PH_FACT_ELIM, PH_MATVEC, PH_KAPPA, PH_AFFINE, PH_REFINE_APPLY, PH_N = 32 };
 #ifdef QPK_PHASE_TIMING
-static __shared__ long long qpk_pt[PH_N];  // the last entry: the previous mark's clock
+static __shared__ long long qpk_pt[PH_N];
 #define QPK_PT(k)                                       \
   do {                                                  \
     __syncthreads();                                    \
