@@ -89,9 +89,7 @@ template <> struct Vec4<gf> { typedef gf4 type; };
 template <> struct Vec4<const lf> { typedef const lf4 type; };
 template <> struct Vec4<const gf> { typedef const gf4 type; };
 typedef float f2v __attribute__((ext_vector_type(2)));
-template <class F> struct Vec2;
-template <> struct Vec2<lf> { typedef const __attribute__((address_space(3))) f2v type; };
-template <> struct Vec2<gf> { typedef const __attribute__((address_space(1))) f2v type; };
+typedef const __attribute__((address_space(3))) f2v clf2;
 
 // The thread's index and a uniform size, as values the compiler cannot trace
 // back.  The Newton loop inlines every phase; known as loop invariants, each
@@ -133,14 +131,6 @@ QPD T *rflp(T *p) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return (T *)(uintptr_t)(((uint64_t)hi << 32) | lo);
   }
-}
-
-// Orders LDS / global accesses of one wavefront (lanes exchange data
-// through memory without a workgroup barrier).
-QPD void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Optional per-phase cycle counters for profiling builds (-DQPK_PHASE_TIMING):
@@ -387,8 +377,8 @@ __host__ __device__ inline Layout make_layout(int n, int m, int p, int kb, bool 
   const int b4 = b3 + 5 * sn;
   L.y = b4; L.b = b4 + sp; L.re = b4 + 2 * sp;
   const int b5 = b4 + 3 * sp;
-  // M's storage ends with 16 floats past the last row: a zero row for the
-  // triangular solves, in M's own address space
+  // in LDS M's storage ends with 16 floats past the last row, a zero row for the
+  // triangular solves (the solves on a factor in global memory need none)
   L.M = m_lds ? b5 : -1;
   L.total = m_lds ? b5 + al4(moff(L.Nmax) + kNB) : b5;
   return L;
@@ -1059,20 +1049,19 @@ QPK_PHASE bool signed_cholesky(MF *M, int N, int npos, li *flag, bool dyn, lf *d
 
 // o[t] = p[t] for t < RPL (p aligned to RPL floats) if `in`, else zeros, as
 // one vector load for RPL <= 4 (16-byte loads above).
-template <int RPL, class MF>
-QPD void load_run(const MF *p, bool in, float (&o)[RPL]) {
+template <int RPL>
+QPD void load_run(const lf *p, bool in, float (&o)[RPL]) {
   if constexpr (RPL == 1) {
     o[0] = in ? p[0] : 0.f;
   } else if constexpr (RPL == 2) {
     f2v v = {0.f, 0.f};
-    if (in) v = *reinterpret_cast<const typename Vec2<MF>::type *>(p);
+    if (in) v = *reinterpret_cast<clf2 *>(p);
     o[0] = v.x; o[1] = v.y;
   } else {
-    typedef typename Vec4<const MF>::type CV4;
 #pragma unroll
     for (int t = 0; t < RPL; t += 4) {
       f4v v = {0.f, 0.f, 0.f, 0.f};
-      if (in) v = *reinterpret_cast<CV4 *>(p + t);
+      if (in) v = *reinterpret_cast<const lf4 *>(p + t);
       o[t] = v.x; o[t + 1] = v.y; o[t + 2] = v.z; o[t + 3] = v.w;
     }
   }
@@ -1096,10 +1085,9 @@ QPD void load_run(const MF *p, bool in, float (&o)[RPL]) {
 // not be touched in a block read the zero row `zrow` (16 zeros stored after
 // M's last row, so both pointers are in M's address space), and rows past N-1
 // hold 0 with an inverse of 0, so the steps carry no tests.
-template <int S, int WG, class MF>
-QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow, int g,
+template <int S, int WG>
+QPD void signed_solve_waves(const lf *M, int N, int npos, lf *r, const lf *zrow, int g,
                             lf *ex, li *bad) {
-  typedef typename Vec4<const MF>::type CV4;
   static_assert(kNB % S == 0, "row slot must be static within a block");
   // columns in flight: two buffers of S x CW floats per lane
   constexpr int CW = S > 4 ? 4 : (S > 2 ? 8 : kNB);
@@ -1107,7 +1095,7 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
   const int lr = S * lane;  // this lane's first local row
   const int i0 = kNB * ((lr >> 4) * WG + g) + (lr & 15);
   float a[S], dl[S];
-  const MF *row[S];
+  const lf *row[S];
 #pragma unroll
   for (int t = 0; t < S; ++t) {
     const bool in = i0 + t < N;
@@ -1123,10 +1111,10 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
     for (int t = 0; t < S; ++t) {
       // rows below the block: L[i][j..]; rows in the block: their lower part
       // with zeros right of the diagonal; finished rows and rows past N-1: zeros
-      const MF *p = i0 >= jb && i0 + t < N ? row[t] + j : zrow + (j & 15);
+      const lf *p = i0 >= jb && i0 + t < N ? row[t] + j : zrow + (j & 15);
 #pragma unroll
       for (int c = 0; c < CW; c += 4) {
-        const f4v v4 = *reinterpret_cast<CV4 *>(p + c);
+        const f4v v4 = *reinterpret_cast<const lf4 *>(p + c);
         nx[t][c] = v4.x; nx[t][c + 1] = v4.y; nx[t][c + 2] = v4.z; nx[t][c + 3] = v4.w;
       }
     }
@@ -1207,7 +1195,7 @@ QPD void signed_solve_waves(const MF *M, int N, int npos, lf *r, const MF *zrow,
     // rows b0 .. b0+15 are one block: row b0+c starts c * rstride floats
     // after row b0 (the last rows, past N-1, read row N-1)
     const int b0 = j & ~15, h = j & 15, rstride = 20 + b0;
-    const MF *brow = M + moff(b0) + i0;
+    const lf *brow = M + moff(b0) + i0;
     // rows above the block read row j; rows in the block read row j's
     // zero padding right of its diagonal; rows below read zeros.  A lane's
     // S rows are all above the block or all at or below it.
@@ -1440,7 +1428,7 @@ QPD void signed_solve_tiles(const gf *M, int N, int npos, lf *r0, lf *r1, bool b
 // bounds them), above that half of the workgroup's waves each.  A barrier must
 // follow.  *bad is set if a solution has a non-finite entry.
 template <int T, int RPL, class MF>
-QPD void signed_solve(const MF *M, int N, int npos, lf *r0, lf *r1, bool both, const MF *zrow,
+QPD void signed_solve(const MF *M, int N, int npos, lf *r0, lf *r1, bool both, const lf *zrow,
                       lf *ex, li *bad) {
   if constexpr (std::is_same<MF, lf>::value) {
     constexpr int WG = RPL > 4 ? T / 128 : 1, S = RPL / WG;
@@ -1518,7 +1506,7 @@ QPD void kkt_matvecs(const gf *Q, const gf *G, const gf *A, int n, int m, int p,
     // with x into out
     auto sweep = [&](const gf *R, int rows, const lf *w, bool cols, la *out, bool dots,
                      AT(&c)[4]) {
-          for (int i0 = 0; i0 < rows; i0 += U * RG) {
+      for (int i0 = 0; i0 < rows; i0 += U * RG) {
         float e[U][4];
         load_rows<T, U>(R, n, rows, n, i0, jb, e);
 #pragma unroll
@@ -1594,7 +1582,7 @@ struct Ctx {
   lf *rt, *ri, *re, *rz, *rs, *tGz, *tAy;
   lf *t0, *t1, *u0, *u1, *dv0, *dv1, *ex, *part, *red;
   lf *w0, *w1, *rr, *rd;  // w0, w1: rhs copies of the refinement (in t0, t1)
-  MF *mz;  // 16 zeros after M's last row (same address space as M)
+  lf *mz;  // 16 zeros after the last row of a factor in LDS
   ldd *dd;
   li *role, *bidx, *elist, *iflag;
   lf *stg;  // matrix-core assembly staging (aliases part .. ex)
@@ -1627,9 +1615,13 @@ QPD void place(CT &C) {
   C.elist = reinterpret_cast<li *>(sm + L.elist);
   C.iflag = reinterpret_cast<li *>(sm + L.iflag);
   C.stg = sm + L.stg;
-  if constexpr (mlds) C.M = sm + L.M;
-  else C.M = C.Mg;
-  C.mz = C.M + moff(L.Nmax);
+  if constexpr (mlds) {
+    C.M = sm + L.M;
+    C.mz = C.M + moff(L.Nmax);
+  } else {
+    C.M = C.Mg;
+    C.mz = sm;  // (not read)
+  }
 }
 
 // Uniform copy of a context (see rfl) with its addresses.
@@ -3019,7 +3011,9 @@ QPD void load_vectors(CT &C) {
   for (int i = tid; i < C.n; i += T) C.q[i] = C.q_g[i];
   for (int i = tid; i < C.m; i += T) C.h[i] = C.h_g[i];
   for (int i = tid; i < C.p; i += T) C.b[i] = C.b_g[i];
-  if (tid < kNB) C.mz[tid] = 0.f;
+  if constexpr (std::is_same<typename CT::MT, lf>::value) {
+    if (tid < kNB) C.mz[tid] = 0.f;
+  }
   __syncthreads();
 }
 
