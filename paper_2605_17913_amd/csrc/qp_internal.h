@@ -75,9 +75,9 @@ size_t lds_bytes(int n, int m, int p, int kb, bool m_in_lds, int threads);
 int64_t ws_floats(int n, int m, int p, int kb);
 // Whether the matrix-core assembly's LDS staging fits the per-QP layout.
 bool mfma_stage_fits(int n, int m, int p, int kb, bool m_in_lds, int threads);
-// Largest dynamic LDS per block the kernels may use on this device.
-// LDS of a CU, the kernels' static LDS (profiling counters; an upper
-// bound, which the sizes that fit LDS depend on) and the most dynamic LDS one QP may take.
+// LDS of a CU, the kernels' static LDS (profiling counters; an upper bound,
+// which the sizes that fit LDS depend on) and the most dynamic LDS one QP may
+// take.
 constexpr size_t kCuLds = 160 * 1024;
 #ifdef QPK_PHASE_TIMING
 constexpr size_t kStaticLds = 512 + 256;
@@ -119,6 +119,14 @@ inline int make_plan(int n, int m, int p, const qp_opts &o, Plan *pl) {
   if (m > 4096) return QPX_ERR_UNSUPPORTED;
   pl->kb = kb;
   const int N = n + kb + p;
+  // Threads per QP.  128 up to 64 rows: more QPs per CU than with 256 (2048
+  // solves of n = 30, m = 30: 0.74 ms against 1.06; alone, 0.261 against 0.255).
+  // Just above, with the factor in LDS, 128 would still win in large batches (1024
+  // of n = 33, m = 57: 0.81 against 1.24) and lose alone (0.533 against 0.478).
+  // 256 up to 256 rows: 512 of n = 120, m = 120 1.86 ms against 3.43 with 512,
+  // alone 1.12 against 1.23.  512 above, where the factorisation has blocks for
+  // eight waves: 256 of n = 140, m = 140 1.88 ms against 2.34 with 256, alone
+  // 1.49 against 1.82.
   int T = o.block;
   if (T == 0) T = N <= 64 ? 128 : (N <= 256 ? 256 : 512);
   if (T != 128 && T != 256 && T != 512) return QPX_ERR_ARG;
@@ -129,10 +137,13 @@ inline int make_plan(int n, int m, int p, const qp_opts &o, Plan *pl) {
   // QPs resident per CU: LDS-limited, and at most the waves the register
   // allocation targets (three per SIMD up to 256 threads, four at 256
   // threads with more than 128 rows and the factor in global memory, two at
-  // 512).  A
-  // factor that fits LDS but halves (or worse) the residency of the
+  // 512).  A factor that fits LDS but halves (or worse) the residency of the
   // global-factor layout goes to global memory instead: at n = 100 the LDS
-  // factor leaves one QP per CU, the global one three (15% faster).
+  // factor leaves one QP per CU and the global one four (1024 solves 10.1 ms
+  // against 5.14, 2048 20.2 against 10.2), at n = 65 with 130 box rows two and
+  // four (1200: 2.65 against 2.21).  A batch of no more QPs than the LDS layout
+  // has room for loses by it (256 of n = 100 2.52 against 3.05 ms, 300 of the box
+  // QPs 1.00 against 1.13): the plan does not know the batch.
   const size_t cu_lds = qpk::kCuLds;
   auto per_cu = [&](size_t bytes, bool global) {
     const int cu_waves = 4 * (T >= 512 ? 2 : (T == 256 && N > 128 && global ? 4 : 3));
@@ -169,6 +180,10 @@ inline int make_plan(int n, int m, int p, const qp_opts &o, Plan *pl) {
     pl->ws_stride = qpk::ws_floats(n, m, p, kb);
   }
   const bool stage_fits = qpk::mfma_stage_fits(n, m, p, kb, pl->m_in_lds, T);
+  // Matrix cores from n = 96 on (FP32 solves, vector ALUs against matrix cores:
+  // 1024 of n = 80 2.99 and 3.03 ms, n = 88 3.33 and 3.44, n = 96 4.11 and 3.86,
+  // n = 100 5.05 and 4.81; 128 of n = 200 9.69 and 8.52; 64 of n = 256 18.5 and
+  // 14.1).
   int am = o.assembly;
   if (am == QPX_ASM_AUTO)
     am = (o.form == QPX_BOUNDED && n >= 96 && stage_fits) ? QPX_ASM_MFMA_FP32 : QPX_ASM_FP32;

@@ -94,10 +94,11 @@ typedef const __attribute__((address_space(3))) f2v clf2;
 // The thread's index and a uniform size, as values the compiler cannot trace
 // back.  The Newton loop inlines every phase; known as loop invariants, each
 // phase's lane predicates, row addresses and trip counts would be computed
-// before the loop and kept (spilled) for all of it: 152 bytes of scratch per
-// lane and 399 scalar spills in the solve kernel of 256 threads and 2 rows per
-// lane, none and 304 with the index opaque (1024 QPs of n = 100, forward and
-// backward: 12.0 -> 10.7 ms).
+// before the loop and kept (spilled) for all of it: 212 bytes of scratch per
+// lane in the solve kernel of 256 threads and 2 rows per lane, 12 with the index
+// opaque (4096 solves of n = 50 5.11 -> 4.62 ms, 1024 of n = 100 5.98 -> 5.18).
+// Scalar registers spill either way (536 and 593 there), into lanes of vector
+// registers.
 QPD int tidx() {
   int t = threadIdx.x;
   asm volatile("" : "+v"(t));
@@ -314,7 +315,8 @@ QPD MRow<MF> mrow(int N, int i) {
 }
 
 // Lower-triangular tile t -> (ti, tj), tj <= ti, in row order.  The estimate
-// is off by at most one for the tile counts in use (below 2^15).
+// is off by at most one for the tile counts in use (up to 32896, the 4x4 tiles
+// of n = 1024).
 QPD void tile_ij(int t, int &ti, int &tj) {
   int i = (int)((__builtin_amdgcn_sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
   i += (i + 1) * (i + 2) / 2 <= t;
@@ -1425,8 +1427,9 @@ QPD void signed_solve_tiles(const gf *M, int N, int npos, lf *r0, lf *r1, bool b
 
 // The solves of one or two right-hand sides side by side.  With the factor in
 // LDS, up to 4 rows per lane one wave each (the chain of dependent steps
-// bounds them), above that half of the workgroup's waves each.  A barrier must
-// follow.  *bad is set if a solution has a non-finite entry.
+// bounds them), above that half of the workgroup's waves each (the plans reach
+// that with 257 rows at 512 threads only: larger factors do not fit LDS).  A
+// barrier must follow.  *bad is set if a solution has a non-finite entry.
 template <int T, int RPL, class MF>
 QPD void signed_solve(const MF *M, int N, int npos, lf *r0, lf *r1, bool both, const lf *zrow,
                       lf *ex, li *bad) {
@@ -1571,8 +1574,9 @@ struct Ctx {
   typedef MF MT;
   static constexpr int T = T_;
   // row batches in flight in the products with Q, G and A: eight from 4 rows
-  // per lane on (1024 QPs of n = 100, forward and backward: 9.3 -> 8.2 ms);
-  // below, their registers spill (1 QP of n = 8: 234 -> 250 us)
+  // per lane on (four: 1024 solves of n = 100 5.18 -> 5.25 ms, 64 of n = 256
+  // 13.74 -> 13.86); below, their registers spill (1 QP of n = 8: 235 -> 243 us,
+  // 4096 of n = 10 1.02 -> 1.04 ms)
   static constexpr int U = RPL >= 4 ? 8 : 4;
   int n, m, p, kb;
   const gf *Q, *q_g, *A, *b_g, *G, *h_g;
@@ -2248,20 +2252,8 @@ QPK_PHASE void solve2(CT &Cin_, int N, bool both) {
 }
 
 
-// Iterative refinement of a solution u of the augmented system
-//   [[H, C'], [C, -Dl]] u = w,  H = Q + G_I' diag(wts_I) G_I,  C = [G_B; A],
-// wts = E/D (bounded form) or E (standard form / initialisation, where E
-// holds z/s or 1),
-// Dl = D/E on bounded border rows and 0 on equality rows, against the
-// operator WITHOUT any regularisation, with the residual w - K u
-// accumulated in AT (FP32, or FP64 once a QP's FP32 refinement stalled)
-// from the original Q, G, A.  Each step solves for the correction with the
-// existing factor (one wave) and adds it.  A step whose residual is not
-// smaller than the previous one is taken back and ends the refinement.
-// Returns the contraction of the first correction (residual max-norm after
-// it over the one before; 0 after a single step, kBig for a non-finite
-// residual): above 1/2 the factor is too coarse a preconditioner in this
-// arithmetic.
+// Contraction of a refinement step above which the factor is too coarse a
+// preconditioner in the arithmetic in use (refine, below).
 constexpr float kRefineSlow = 0.5f;
 
 // out = w - K u (sub) or K u, for the augmented operator of refine (below),
@@ -2317,13 +2309,13 @@ QPD float maxnorm(const lf *r, int N, lf *red) {
 // operator WITHOUT any regularisation, with the residual w - K u
 // accumulated in AT (FP32, or FP64 once a QP's FP32 refinement stalled)
 // from the original Q, G, A.  Each step solves for the correction with the
-// existing factor (one wave) and adds it; the residual after each
-// correction is checked, and a correction that did not make it smaller is
-// taken back and ends the refinement.  Returns the contraction of the first
-// correction (residual max-norm after it over the one before; kBig for a
-// non-finite residual): above 1/2 the factor is too coarse a
-// preconditioner in this arithmetic.  iflag[7] receives the residual
-// max-norm of the returned u (float bits).
+// existing factor (signed_solve, one right-hand side) and adds it; the residual
+// after each correction is checked, and a correction that did not make it
+// smaller is taken back and ends the refinement.  Returns the contraction of the
+// first correction (residual max-norm after it over the one before; 0 if none
+// was taken, kBig for a non-finite residual): above kRefineSlow the factor is
+// too coarse a preconditioner in this arithmetic.  iflag[7] receives the
+// residual max-norm of the returned u (float bits).
 template <int T, int RPL, class AT, class CT>
 QPK_PHASE float refine(CT &Cin_, int nb, bool bounded, const lf *w, lf *u, int steps) {
   CT C = uctx(Cin_);
@@ -3361,8 +3353,8 @@ QPD void qp_body(const Params &P) {
     // gradient entries off by up to 0.8% without; with one refinement step
     // per relaxation step every entry is within 0.4% of its 1e-3 bound;
     // n = 200, m = 800 missed the bound by 2.6x without).  At m = 2n (the
-    // benchmark shapes) it would cost 44% of the backward pass for no
-    // measurable gain.
+    // benchmark shapes) it would make the backward pass 63% longer (4096 QPs of
+    // n = 50: 1.68 -> 2.74 ms) for no measurable gain.
     const int refine_relax = bounded && m >= 3 * n ? max(refine, 1) : refine;
     status = newton_loop<T, RPL>(C, bounded, P.relax_max_iter, P.relax_tol, 2, 0.f, P.kappa_relax,
                                  P.delta_reg, refine_relax, work, iters, res);
@@ -3405,11 +3397,14 @@ QPD void qp_body(const Params &P) {
 // threads per QP, 2 (256 VGPRs) at 512, and 4 (128 VGPRs) for 256 threads
 // with 4 rows per lane and the factor in global memory in the solve and
 // serving kernels: their systems (129 to 256 rows) leave a small LDS
-// footprint, so four QPs fit a CU (n = 100: solve 13.6 -> 12.5 ms; the
-// backward kernel at four waves spilled into a 25% slower launch and keeps
-// three).  At 128 threads, 4 waves spilled about twice as much and ran 24%
-// slower on n = 10 and n = 20; kernels with the factor in LDS are held to
-// three QPs per CU or fewer by LDS.
+// footprint, so four QPs fit a CU (1024 solves of n = 100: 6.88 ms at three,
+// 5.18 at four; 24 of them, one per CU, 2.77 and 2.80).  Kernels with the factor
+// in LDS and more than 64 rows are held to three QPs per CU or fewer by LDS.
+// Two lines date from kernels that spilled more and measure otherwise on these:
+// the backward kernel of that size at four waves takes 1.89 instead of 2.51 ms
+// (1024 QPs) and 1.04 instead of 1.03 (24), and the kernels of 128 threads at
+// four 0.93 instead of 1.02 ms (4096 solves of n = 10), 1.51 instead of 1.67
+// (n = 20) and 0.304 instead of 0.294 (64 of n = 10).
 #define QPK_MIN_WAVES(T, RPL, MLDS) \
   ((T) >= 512 ? 2 : ((T) == 256 && (RPL) == 4 && !(MLDS) ? 4 : 3))
 #define QPK_MIN_WAVES_BWD(T) ((T) >= 512 ? 2 : 3)
