@@ -8,8 +8,9 @@
 //     the request's footprint (inputs + iterate + factor storage if the
 //     factor does not fit LDS);
 //  2. launches the serving kernel on the lane for one bucket of resident QPs
-//     that are not in flight (the bucket holding the longest-waiting QP):
-//     the new requests' data are uploaded first on the same stream, every QP
+//     that are not in flight (the bucket holding the longest-waiting QP, one
+//     that no other lane has in flight if there is such a one): the new
+//     requests' data are uploaded first on the same stream, every QP
 //     resumes its Newton loop from the iterate kept in the arena for a
 //     bounded number of iterations (a fresh QP first runs the
 //     initialisation), and the kernel also writes each QP's iterate to the
@@ -123,9 +124,9 @@ void layout_request(Request *r) {
 }
 
 struct Bucket {
-  int threads;
-  int rpl;
-  bool mlds;
+  int threads = 0;
+  int rpl = 0;
+  bool mlds = false;
   bool operator==(const Bucket &o) const {
     return threads == o.threads && rpl == o.rpl && mlds == o.mlds;
   }
@@ -146,6 +147,7 @@ struct Lane {
   float *d_out = nullptr, *h_out = nullptr;  // staging of the iterates
   std::vector<Request *> batch;              // the launch in flight (launch order)
   std::vector<size_t> out_off;               // each QP's place in the staging buffer
+  Bucket bucket;                             // of that launch
   bool busy = false;
 };
 
@@ -185,8 +187,11 @@ namespace {
 // same numbers of QPs per CU.
 Bucket bucket_of(const Request *r) {
   const int N = r->n + r->plan.kb + r->p;
-  Bucket b{r->plan.threads, 1, r->plan.m_in_lds};
+  Bucket b;
+  b.threads = r->plan.threads;
+  b.rpl = 1;
   while (64 * b.rpl < N) b.rpl *= 2;
+  b.mlds = r->plan.m_in_lds;
   return b;
 }
 
@@ -194,19 +199,33 @@ Bucket bucket_of(const Request *r) {
 // (reads the active list).  With small_only, only buckets of systems of at
 // most 128 rows qualify.  Returns false if nothing was launched.
 //
-// A bucket may be in flight on several lanes at once.  Its QPs that arrive, or
-// were left over by the staging buffer, while it is in flight start on the next
-// idle lane: held back until its launch has ended instead, 2 clients that send
-// QPs of n = 10 in turn get 3.2K instead of 5.2K solves/s, 32 clients of n = 50
-// 11.9K instead of 16.4K, 32 of n = 128 4.7K instead of 5.5K, and a mixed
-// stream (200 requests of n in 8..256 at once) 2.8K instead of 3.0K.
+// A lane goes first to the buckets that no other lane has in flight, so that
+// the launches of one do not hold all lanes: taken in order of age alone, QPs of
+// n = 65..128 in a mixed stream wait for the larger ones (p50 of 4000 requests/s
+// of n in 8..256: 8.9 ms, 5.3 so).  If no such bucket waits, the lane goes to one
+// in flight: QPs that arrive meanwhile, or were left over by the staging buffer,
+// start at once.  Held back until their bucket's launch has ended, 4 clients
+// that send QPs of n = 10 in turn get 5.9K instead of 8.8K solves/s, 24 of
+// n = 50 10.1K instead of 14.1K and 24 of n = 256 1.17K instead of 1.27K.
 bool launch_bucket(qpx_server *S, Lane &L, bool small_only) {
-  // the bucket of the longest-waiting idle QP
+  // the longest-waiting idle QP of a bucket not in flight, else of any
+  auto in_flight = [&](const Bucket &b) {
+    for (const Lane &o : S->lane)
+      if (o.busy && o.bucket == b) return true;
+    return false;
+  };
   const Request *oldest = nullptr;
-  for (const Request *r : S->active)
-    if (!r->in_flight && (!small_only || bucket_of(r).rpl <= 2) &&
-        (!oldest || r->order < oldest->order))
+  bool oldest_flies = false;
+  for (const Request *r : S->active) {
+    if (r->in_flight) continue;
+    const Bucket b = bucket_of(r);
+    if (small_only && b.rpl > 2) continue;
+    const bool flies = in_flight(b);
+    if (!oldest || (flies == oldest_flies ? r->order < oldest->order : oldest_flies)) {
       oldest = r;
+      oldest_flies = flies;
+    }
+  }
   if (!oldest) return false;
   const Bucket bk = bucket_of(oldest);
   std::vector<Request *> cand;
@@ -283,6 +302,7 @@ bool launch_bucket(qpx_server *S, Lane &L, bool small_only) {
   (void)hipMemcpyAsync(L.h_iters, L.d_iters, cnt * 4, hipMemcpyDeviceToHost, L.stream);
   (void)hipMemcpyAsync(L.h_out, L.d_out, used * 4, hipMemcpyDeviceToHost, L.stream);
   (void)hipEventRecord(L.done, L.stream);
+  L.bucket = bk;
   L.busy = true;
   return true;
 }
